@@ -1,0 +1,694 @@
+"""Timed workloads of the PPM library, through its public entry points.
+
+Every case is one step (or one root step of the W-cycle) of a state that
+lives on the device, as a simulation's main loop takes it:
+
+  grid     one periodic patch: ppm_fill_periodic + ppm_step_cfl on a plan, or
+           the same as a captured graph; with sources also ppm_expansion
+  noalloc  one periodic patch through ppm_step_cfl_noalloc
+  batch    many uneven AMR patches with given ghosts, flux registers on
+  hier     a periodic root and uneven patches on levels 1-8 in one plan, one
+           captured graph per step (fill, CFL, step)
+  amr      ppm_amr_step on a nested three-level hierarchy
+
+Sweep orders alternate xyz / zyx from pass to pass.  `exact` holds the
+method's formulas in plain torch, 64 bits, one operation at a time.
+"""
+import math
+
+import torch
+
+from paper_1307_2265_amd import autotune, ppm
+from paper_1307_2265_amd import workloads as W
+
+GAMMA, CFL, ETA1, ETA2 = 5.0 / 3.0, 0.4, 1e-3, 0.1
+FLOOR, E_FLOOR, RTOL, MAX_ITER = 1e-20, 1e-30, 1e-13, 20
+FIELDS = ("rho", "vx", "vy", "vz", "etot", "eint")
+ORDERS = ((0, 1, 2), (2, 1, 0))
+FLOPS = 669.0  # FP64 operations of one cell in one sweep (data/algorithmic_ops.json)
+EXPANSION = (1.7, 0.6)  # a, adot of the cases with sources
+
+# sigma of ln rho, velocity rms per component over c_ref, pressure: uniform
+# amplitude or (negative) sigma of ln p.  Gentle subsonic noise, and strongly
+# shocked flow (rms Mach 5, density contrast ~1e3).
+RECIPES = {"gentle": (0.5, 0.5, 0.1), "shocked": (2.0, 5.0 / math.sqrt(3.0), -1.0)}
+
+
+def _grid(name, n, prec, recipe, **more):
+    nx, ny, nz = n if isinstance(n, tuple) else (n, n, n)
+    return dict(dict(name=name, kind="grid", nx=nx, ny=ny, nz=nz, ghost=3, prec=prec,
+                     recipe=recipe, solver="two-shock", diffusion=False, sources=False,
+                     graph=False), **more)
+
+
+def listed():
+    return [
+        # a unit-test or parameter-scan sized box: launches and latency
+        _grid("grid16", 16, "fp64", "gentle"),
+        # the small parity grid, from a loop that may not allocate
+        dict(_grid("noalloc32", 32, "fp64", "gentle"), kind="noalloc"),
+        # a small production box replayed as a graph
+        _grid("grid64_mixed", 64, "mixed", "gentle", graph=True),
+        # a ragged box with the HLLC solver, the diffusive flux and four ghosts
+        _grid("ragged_hllc", (97, 61, 83), "fp64", "shocked", solver="hllc", diffusion=True,
+              ghost=4),
+        # a medium comoving box with gravity
+        _grid("grid128_gravity", 128, "fp64", "gentle", sources=True),
+        # the gentle 256^3 and the headline 512^3 grids
+        _grid("grid256", 256, "fp64", "gentle"),
+        _grid("grid512", 512, "fp64", "shocked"),
+        _grid("grid512_mixed", 512, "mixed", "shocked"),
+        # the batched form: 4096 patches with the autotuned launch shapes as a
+        # graph, and a small level of a hierarchy with the default plan
+        dict(name="batch4096", kind="batch", npatch=4096, layout=1003, prec="fp64",
+             recipe="shocked", solver="two-shock", tuned=True, graph=True),
+        dict(name="batch300_mixed", kind="batch", npatch=300, layout=7, prec="mixed",
+             recipe="shocked", solver="two-shock", tuned=False, graph=False),
+        # a quarter-scale cosmology-shaped hierarchy in one plan
+        dict(name="hier256", kind="hier", n=256, npatch=400, layout=1004, prec="fp64",
+             recipe="gentle"),
+        # the W-cycle on the nested benchmark hierarchy
+        dict(name="amr128", kind="amr", n=128, dim1=32, per1=4, dim2=24, per2=2, prec="fp64",
+             recipe="gentle"),
+    ]
+
+
+def draw(rng):
+    prec = rng.choice(("fp64", "fp64", "mixed"))
+    recipe = rng.choice(("gentle", "shocked"))
+    kind = rng.choice(("grid", "grid", "grid", "noalloc", "batch", "batch", "hier", "amr"))
+    if kind in ("grid", "noalloc"):
+        edge = math.exp(rng.uniform(math.log(8), math.log(400 if kind == "grid" else 160)))
+        n = [max(4, round(edge * math.exp(rng.uniform(-0.3, 0.3)))) for _ in range(3)]
+        c = _grid("", tuple(n), prec, recipe, ghost=rng.choice((3, 3, 4)), kind=kind)
+        if kind == "grid":
+            c["solver"] = rng.choice(("two-shock", "two-shock", "hllc"))
+            c["diffusion"] = rng.random() < 0.15
+            c["sources"] = rng.random() < 0.2
+            c["graph"] = rng.random() < 0.3
+        del c["name"]
+        return c
+    if kind == "batch":
+        return dict(kind=kind, npatch=round(math.exp(rng.uniform(math.log(3), math.log(4000)))),
+                    layout=rng.randrange(10000), prec=prec, recipe=recipe,
+                    solver=rng.choice(("two-shock", "two-shock", "hllc")), tuned=rng.random() < 0.5, graph=rng.random() < 0.5)
+    if kind == "hier":
+        return dict(kind=kind, n=rng.randrange(64, 257), npatch=rng.randrange(30, 400),
+                    layout=rng.randrange(10000), prec=prec, recipe=recipe)
+    return dict(kind=kind, n=rng.choice((48, 64, 80, 96, 112)), dim1=rng.choice((16, 20, 24)),
+                per1=rng.choice((1, 2)), dim2=rng.choice((12, 16)), per2=1, prec=prec,
+                recipe="gentle")
+
+
+# ---------------------------------------------------------------------------
+# inputs
+
+
+def _gen(seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(int(seed))
+    return g
+
+
+def _cells(count, recipe, gen, prec):
+    """The six stored fields of `count` independent random cells (flat)."""
+    sr, sv, sp = RECIPES[recipe]
+
+    def normal():
+        return torch.randn(count, generator=gen, device="cuda", dtype=torch.float64)
+
+    f = {"rho": torch.exp(sr * normal() - 0.5 * sr * sr)}
+    for k in ("vx", "vy", "vz"):
+        f[k] = sv * math.sqrt(GAMMA) * normal()
+    if sp > 0:
+        u = torch.rand(count, generator=gen, device="cuda", dtype=torch.float64)
+        p = 1.0 + sp * (2.0 * u - 1.0)
+    else:
+        p = torch.exp(-sp * normal() - 0.5 * sp * sp)
+    for k in ("rho", "vx", "vy", "vz"):  # both precisions start from the same stored values
+        f[k] = f[k].float()
+        if prec == "fp64":
+            f[k] = f[k].double()
+    f["eint"] = p / ((GAMMA - 1.0) * f["rho"].double())
+    f["etot"] = f["eint"] + 0.5 * sum(f[k].double().square() for k in ("vx", "vy", "vz"))
+    return {k: f[k] for k in FIELDS}
+
+
+def _waves(shape, gen, dtype, amp=3.0):
+    """A smooth acceleration field: per component four plane waves over the box."""
+    ax = [torch.arange(n, dtype=torch.float64, device="cuda") / n for n in shape]
+    out = []
+    for _ in range(3):
+        k = torch.randint(1, 4, (4, 3), generator=gen, device="cuda").tolist()
+        ph = (2 * math.pi * torch.rand(4, generator=gen, device="cuda")).tolist()
+        w = torch.randn(4, generator=gen, device="cuda").tolist()
+        a = torch.zeros(shape, dtype=torch.float64, device="cuda")
+        for (kz, ky, kx), p, m in zip(k, ph, w):
+            a += m * torch.sin(2 * math.pi * (kz * ax[0][:, None, None] + ky * ax[1][:, None]
+                                              + kx * ax[2]) + p)
+        out.append((amp / 2.0 * a).to(dtype))
+    return tuple(out)
+
+
+def _single(case, seed):
+    """(fields of the ghosted box, acceleration or None) of a periodic patch."""
+    g, gen = case["ghost"], _gen(seed)
+    n = (case["nz"], case["ny"], case["nx"])
+    full = tuple(v + 2 * g for v in n)
+    act = _cells(n[0] * n[1] * n[2], case["recipe"], gen, case["prec"])
+    f = {}
+    for k in FIELDS:
+        f[k] = torch.zeros(full, dtype=act[k].dtype, device="cuda")
+        f[k][g:-g, g:-g, g:-g] = act.pop(k).view(n)
+    return f, _waves(full, gen, f["rho"].dtype) if case["sources"] else None
+
+
+def _specs(case):
+    """(dims (nx, ny, nz), level, dx) of the patches of a batch or hierarchy."""
+    if case["kind"] == "batch":
+        return [((s.nx, s.ny, s.nz), s.level, s.dx)
+                for s in W.patch_specs(case["npatch"], case["layout"])]
+    n = case["n"]
+    return [((n, n, n), 0, 1.0 / n)] + [
+        ((s.nx, s.ny, s.nz), s.level, s.dx)
+        for s in W.hierarchy_specs(case["npatch"], n, case["layout"])]
+
+
+def _flat(dims, recipe, seed, prec, ghost=3):
+    """Fields of patches back to back, and each patch's slice and shape."""
+    shapes = [tuple(v + 2 * ghost for v in reversed(d)) for d in dims]
+    offs = [0]
+    for s in shapes:
+        offs.append(offs[-1] + s[0] * s[1] * s[2])
+    return _cells(offs[-1], recipe, _gen(seed), prec), offs, shapes
+
+
+# ---------------------------------------------------------------------------
+# states and passes
+
+
+def _prec(case):
+    return ppm.PPM_FP64 if case["prec"] == "fp64" else ppm.PPM_MIXED
+
+
+def _params(case):
+    flags = ppm.PPM_ALL_FLAGS
+    if case.get("solver") == "hllc":
+        flags |= ppm.PPM_HLLC
+    if case.get("diffusion"):
+        flags |= ppm.PPM_DIFFUSION
+    return ppm.params(flags=flags)
+
+
+def _patches(case, seed):
+    """Patches of a batch, a hierarchy plan or a nested hierarchy."""
+    if case["kind"] == "amr":
+        hier = W.nested_hierarchy(case["n"], (case["dim1"], case["dim2"]),
+                                  (case["per1"], case["per2"]))
+        specs = [(h.dims, h.level, 0.5 ** h.level / case["n"]) for h in hier]
+        places = [(h.parent, 2, h.start) for h in hier]
+    else:
+        specs, places = _specs(case), None
+    flat, offs, shapes = _flat([d for d, _, _ in specs], case["recipe"], seed, case["prec"])
+    rsz = [ppm.ppm_flux_reg_size(*d) for d, _, _ in specs]
+    reg = torch.zeros(sum(rsz), dtype=torch.float64, device="cuda")
+    out, r = [], 0
+    for i, (d, level, dx) in enumerate(specs):
+        root = case["kind"] != "batch" and i == 0
+        out.append(ppm.Patch(**{k: flat[k][offs[i]:offs[i + 1]].view(shapes[i]) for k in FIELDS},
+                             dx=dx, dy=dx, dz=dx, level=level, flux_reg=reg[r:r + rsz[i]],
+                             bc=ppm.PPM_BC_PERIODIC if root else ppm.PPM_BC_SUPPLIED))
+        r += rsz[i]
+    return out, places, flat, reg
+
+
+def prepare(case, seed):
+    kind, prec, prm = case["kind"], _prec(case), _params(case)
+    s = {"case": case, "step": 0}
+    if kind in ("grid", "noalloc"):
+        f, acc = _single(case, seed)
+        d = 1.0 / max(case["nx"], case["ny"], case["nz"])
+        s["patches"] = [ppm.Patch(**f, dx=d, dy=d, dz=d, ghost=case["ghost"], accel=acc)]
+        s["flat"], nlevels = f, 1
+    else:
+        s["patches"], places, s["flat"], s["reg"] = _patches(case, seed)
+        nlevels = {"batch": 7, "hier": 9, "amr": 3}[kind]
+    s["prm"] = prm
+    if kind == "amr":
+        s["amr"] = ppm.Amr(s["patches"], places, nlevels, prec, prm)
+        return s
+    s["dt"] = torch.zeros(nlevels, dtype=torch.float64, device="cuda")
+    tiles = autotune.best_tiles("batch/" + case["prec"]) if case.get("tuned") else None
+    plan = ppm.Plan(s["patches"], nlevels, prec, prm, tile_config=tiles)
+    if case.get("sources"):
+        s["expand"] = torch.tensor(EXPANSION, dtype=torch.float64, device="cuda")
+        plan.ppm_set_expansion(s["expand"])
+    if kind != "batch":
+        plan.ppm_fill_periodic()
+    plan.ppm_cfl_dt(s["dt"])
+    s["plan"] = plan
+    if kind == "noalloc":
+        plan.close()
+    elif kind == "hier":
+        s["graphs"] = [ppm.Graph(plan, s["dt"], o, ppm.PPM_GRAPH_FILL | ppm.PPM_GRAPH_CFL
+                                 | ppm.PPM_GRAPH_STEP) for o in (0, 1)]
+    elif case["graph"]:
+        parts = ppm.PPM_GRAPH_STEP_CFL | (ppm.PPM_GRAPH_FILL if kind == "grid" else 0)
+        s["graphs"] = [ppm.Graph(plan, s["dt"], o, parts) for o in (0, 1)]
+    return s
+
+
+def run(s):
+    case, order = s["case"], s["step"] % 2
+    s["step"] += 1
+    out = dict(s["flat"])
+    if "reg" in s:
+        out["flux_reg"] = s["reg"]
+    if case["kind"] == "amr":
+        s["amr"].ppm_amr_step()
+        return out
+    if case["kind"] == "noalloc":
+        ppm.ppm_step_cfl_noalloc(s["patches"], 1, _prec(case), s["prm"], s["dt"], order,
+                                 ppm.PPM_NOALLOC_FILL)
+    else:
+        if case.get("sources"):
+            s["plan"].ppm_expansion(s["dt"])
+        if "graphs" in s:
+            s["graphs"][order].ppm_graph_launch()
+        else:
+            if case["kind"] == "grid":
+                s["plan"].ppm_fill_periodic()
+            s["plan"].ppm_step_cfl(s["dt"], order)
+    out["dt"] = s["dt"]
+    return out
+
+
+def work(case):
+    """The state read once and written once; the method's operations over the
+    cells each sweep of an xyz step writes."""
+    if case["kind"] in ("grid", "noalloc"):
+        dims, g, steps = [(case["nx"], case["ny"], case["nz"])], case["ghost"], [1]
+    elif case["kind"] == "amr":
+        hier = W.nested_hierarchy(case["n"], (case["dim1"], case["dim2"]),
+                                  (case["per1"], case["per2"]))
+        dims, g, steps = [h.dims for h in hier], 3, [2 ** h.level for h in hier]
+    else:
+        dims, g = [d for d, _, _ in _specs(case)], 3
+        steps = [1] * len(dims)
+    cell = 48.0 if case["prec"] == "fp64" else 32.0
+    by = fl = 0.0
+    for (nx, ny, nz), k in zip(dims, steps):
+        by += k * 2 * cell * (nx + 2 * g) * (ny + 2 * g) * (nz + 2 * g)
+        if case["kind"] not in ("grid", "noalloc"):
+            by += k * 96.0 * (nx * ny + ny * nz + nx * nz)
+        if case.get("sources"):
+            by += cell / 2 * nx * ny * nz
+        fl += k * FLOPS * nx * ((ny + 2 * g) * (nz + 2 * g) + ny * (nz + 2 * g) + ny * nz)
+    return {"bytes": by, "flops": fl}
+
+
+# ---------------------------------------------------------------------------
+# the method in plain torch, 64 bits.  Fields are (patch, z, y, x).
+
+
+def _ratio_above(a, b, t):
+    return torch.where(b > 0, a > t * b, a / b > t)
+
+
+def _pressure(r, u, a, b, E, e):
+    eps = E - 0.5 * (u * u + a * a + b * b)
+    eps = torch.where(_ratio_above(eps, E, ETA1), eps, e)
+    return ((GAMMA - 1.0) * r * eps).clamp(min=FLOOR)
+
+
+def _signal_dt(f, g, dx, a):
+    """The CFL timestep of each patch of a stack (dx: one width per patch)."""
+    i = (slice(None),) + (slice(g, -g),) * 3
+    r, vx, vy, vz, E, e = (f[k][i] for k in FIELDS)
+    c = torch.sqrt(GAMMA * _pressure(r, vx, vy, vz, E, e) / r)
+    h = dx.view(-1, 1, 1, 1)
+    s = (c + vx.abs()) / h + (c + vy.abs()) / h + (c + vz.abs()) / h
+    return CFL * a / s.flatten(1).amax(1)
+
+
+def _slope(m, q, p):
+    dl, dr, dc = q - m, p - q, 0.5 * (p - m)
+    s = torch.minimum(torch.minimum(dc.abs(), 2 * dl.abs()), 2 * dr.abs())
+    return torch.where(dl * dr > 0, torch.where(dc < 0, -s, s), torch.zeros_like(s))
+
+
+def _pad(x, lo, hi):
+    return torch.nn.functional.pad(x, (lo, hi))
+
+
+def _parabolas(q):
+    """Edges l, r and coefficients dq, q6 of cells 2 .. n-3 for q = (rho, u,
+    v1, v2, p), each (..., n)."""
+    rho, u, p = q[0], q[1], q[4]
+    n = rho.shape[-1]
+    dm = [_pad(_slope(x[..., :-2], x[..., 1:-1], x[..., 2:]), 1, 1) for x in q]
+    face = [-(1.0 / 6.0) * (d[..., 1:] - d[..., :-1]) + 0.5 * (x[..., :-1] + x[..., 1:])
+            for x, d in zip(q, dm)]                       # face j+1/2 at index j
+    c = slice(2, n - 2)
+    m1, p1 = slice(1, n - 3), slice(3, n - 1)
+    left, right = [f[..., m1] for f in face], [f[..., c] for f in face]
+    # contact steepening
+    d2 = _pad((-2.0 * rho[..., 1:-1] + rho[..., 2:]) + rho[..., :-2], 1, 1)
+    rm, rp, pm, pp = rho[..., m1], rho[..., p1], p[..., m1], p[..., p1]
+    drho = rp - rm
+    on = ((d2[..., p1] * d2[..., m1] < 0)
+          & (drho.abs() - 0.01 * torch.minimum(rp.abs(), rm.abs()) > 0)
+          & (GAMMA * 0.1 * drho.abs() * torch.minimum(pp, pm)
+             >= (pp - pm).abs() * torch.minimum(rp, rm)))
+    eta = -(d2[..., p1] - d2[..., m1]) / torch.where(on, 6.0 * drho, torch.ones_like(drho))
+    eta = torch.where(on, (20.0 * (eta - 0.05)).clamp(0, 1), torch.zeros_like(eta))
+    left[0] = torch.where(eta != 0, left[0] * (1 - eta) + (0.5 * dm[0][..., m1] + rm) * eta,
+                          left[0])
+    right[0] = torch.where(eta != 0, right[0] * (1 - eta) + (-0.5 * dm[0][..., p1] + rp) * eta,
+                           right[0])
+    # shock flattening
+    dp, den = pp - pm, p[..., 4:] - p[..., :-4]
+    on = ((dp.abs() > 0.33 * torch.minimum(pp, pm)) & (u[..., m1] - u[..., p1] > 0))
+    ft = (10.0 * (dp / torch.where(den == 0, torch.ones_like(den), den) - 0.75)).clamp(0, 1)
+    ft = torch.where(den == 0, torch.ones_like(ft), ft)
+    ft = _pad(torch.where(on, ft, torch.zeros_like(ft)), 1, 1)
+    fl = torch.maximum(ft[..., 1:-1], torch.where(dp > 0, ft[..., :-2], ft[..., 2:]))
+    out = []
+    for x, l, r in zip(q, left, right):
+        x = x[..., c]
+        l = torch.where(fl != 0, fl * x + (1 - fl) * l, l)
+        r = torch.where(fl != 0, fl * x + (1 - fl) * r, r)
+        flat = (r - x) * (x - l) <= 0
+        d = r - l
+        s, dd = d * (-0.5 * (l + r) + x), d * d * (1.0 / 6.0)
+        l2 = torch.where(s > dd, -2.0 * r + 3.0 * x, l)
+        r2 = torch.where((s <= dd) & (-dd > s), -2.0 * l + 3.0 * x, r)
+        l, r = torch.where(flat, x, l2), torch.where(flat, x, r2)
+        out.append((l, r, r - l, 6.0 * (-0.5 * (l + r) + x)))
+    return out
+
+
+def _trace(par, u, c, lam, right):
+    """The traced state (rho, u, v1, v2, p) of one edge of every cell."""
+    sg = 1.0 if right else -1.0
+    y = [(sg * w * lam).clamp(0, 1) for w in (u + sg * c, u - sg * c, u)]
+
+    def avg(k, y):
+        l, r, dq, q6 = par[k]
+        a = -(2.0 / 3.0) * y + 1.0
+        return -(0.5 * y) * (-a * q6 + dq) + r if right else (0.5 * y) * (a * q6 + dq) + l
+
+    rt, ut, pt = avg(0, y[0]), avg(1, y[0]), avg(4, y[0])
+    C = torch.sqrt(GAMMA * pt * rt)
+    iC, irt = 1.0 / C, 1.0 / rt
+    us, ps = avg(1, y[1]), avg(4, y[1])
+    slow = sg * 0.5 * iC * (-sg * (pt - ps) * iC + (ut - us))
+    zero = torch.zeros_like(slow)
+    slow = torch.where(sg * (u - sg * c) > 0, slow, zero)
+    b0 = torch.where(sg * u > 0, ((pt - avg(4, y[2])) * iC * iC + irt) - 1.0 / avg(0, y[2]), zero)
+    tau = irt - (slow + b0)
+    rs = torch.where(tau > 0, 1.0 / tau, rt)
+    return (rs.clamp(min=FLOOR), C * (-sg * slow) + ut, avg(2, y[2]), avg(3, y[2]),
+            (C * C * slow + pt).clamp(min=FLOOR))
+
+
+def _two_shock(L, R):
+    (rl, ul, v1l, v2l, pl), (rr, ur, v1r, v2r, pr) = L, R
+    G1 = (GAMMA + 1.0) / (2.0 * GAMMA)
+    cl, cr = torch.sqrt(GAMMA * pl * rl), torch.sqrt(GAMMA * pr * rr)
+    ipl, ipr = 1.0 / pl, 1.0 / pr
+    ps = ((cr * pl + cl * pr - cl * cr * (ur - ul)) / (cl + cr)).clamp(min=FLOOR)
+
+    def speeds(ps):
+        wl = cl * torch.sqrt(1.0 + G1 * (ps * ipl - 1.0))
+        wr = cr * torch.sqrt(1.0 + G1 * (ps * ipr - 1.0))
+        iwl, iwr = 1.0 / wl, 1.0 / wr
+        return wl, wr, iwl, iwr, ul - (ps - pl) * iwl, ur + (ps - pr) * iwr
+
+    done = torch.zeros_like(ps, dtype=torch.bool)
+    for _ in range(MAX_ITER):
+        wl, wr, iwl, iwr, usl, usr = speeds(ps)
+        z = (wl * wl + cl * cl) * (0.5 * iwl * iwl * iwl) + \
+            (wr * wr + cr * cr) * (0.5 * iwr * iwr * iwr)
+        pn = (ps - (usr - usl) / z).clamp(min=FLOOR)
+        done = done | ((pn - ps).abs() <= RTOL * pn)
+        ps = torch.where(done, ps, pn)
+        if bool(done.all()):
+            break
+    wl, wr, iwl, iwr, usl, usr = speeds(ps)
+    us = 0.5 * (usl + usr)
+    left = us >= 0
+
+    def K(a, b):
+        return torch.where(left, a, b)
+
+    r, u, p, w, iw = K(rl, rr), K(ul, ur), K(pl, pr), K(wl, wr), K(iwl, iwr)
+    sg = torch.where(left, -1.0, 1.0).to(r.dtype)
+    rs = (1.0 / (1.0 / r - (ps - p) * iw * iw)).clamp(min=FLOOR)
+    head = u + sg * torch.sqrt(GAMMA * p / r)
+    tail = us + sg * torch.sqrt(GAMMA * ps / rs)
+    shock = ps > p
+    first = torch.where(shock, u + sg * (w / r), head)  # the upwind side's outermost wave
+    keep = sg * first <= 0
+    fan = ~shock & ~keep & ~(sg * tail >= 0)
+    t = torch.where(fan, -head / torch.where(fan, tail - head, torch.ones_like(head)),
+                    torch.ones_like(head))
+    t = torch.where(keep, torch.zeros_like(t), t)
+    rb, ub, pb = (torch.where(fan, (1.0 - t) * k + t * s, torch.where(keep, k, s))
+                  for k, s in ((r, rs), (u, us), (p, ps)))
+    v1, v2 = K(v1l, v1r), K(v2l, v2r)
+    fr, eb = rb * ub, pb / ((GAMMA - 1.0) * rb)
+    Eb = eb + 0.5 * (ub * ub + v1 * v1 + v2 * v2)
+    return [fr, fr * ub + pb, fr * v1, fr * v2, fr * Eb + ub * pb, fr * eb, ub]
+
+
+def _davis(L, R):
+    cl, cr = torch.sqrt(GAMMA * L[4] / L[0]), torch.sqrt(GAMMA * R[4] / R[0])
+    return torch.minimum(L[1] - cl, R[1] - cr), torch.maximum(L[1] + cl, R[1] + cr)
+
+
+def _energies(s):
+    e = s[4] / ((GAMMA - 1.0) * s[0])
+    return e + 0.5 * (s[1] * s[1] + s[2] * s[2] + s[3] * s[3]), e
+
+
+def _hllc(L, R):
+    (El, el), (Er, er) = _energies(L), _energies(R)
+    sL, sR = _davis(L, R)
+    fan = (sL < 0) & (sR > 0)
+    ml, mr = L[0] * (sL - L[1]), R[0] * (sR - R[1])
+    S = (R[4] - L[4] + ml * L[1] - mr * R[1]) / torch.where(fan, ml - mr, torch.ones_like(ml))
+    left = torch.where(fan, S >= 0, sL >= 0)
+    r, u, v1, v2, p = (torch.where(left, a, b) for a, b in zip(L, R))
+    E, e, s = torch.where(left, El, Er), torch.where(left, el, er), torch.where(left, sL, sR)
+    fr = r * u
+    F = [fr, fr * u + p, fr * v1, fr * v2, u * (r * E + p), fr * e, u]
+    m = torch.where(fan, r * (s - u), torch.ones_like(r))
+    rs = m / torch.where(fan, s - S, torch.ones_like(s))
+    G = [F[0] + s * (rs - r), F[1] + s * (rs * S - r * u), F[2] + s * (rs * v1 - r * v1),
+         F[3] + s * (rs * v2 - r * v2),
+         F[4] + s * (rs * (E + (S - u) * (S + p / m)) - r * E), F[5] + s * (rs * e - r * e), S]
+    return [torch.where(fan, a, b) for a, b in zip(G, F)]
+
+
+def _hll(L, R):
+    sL, sR = _davis(L, R)
+    U, F = [], []
+    for s in (L, R):
+        E, e = _energies(s)
+        U.append([s[0], s[0] * s[1], s[0] * s[2], s[0] * s[3], s[0] * E, s[0] * e])
+        F.append([s[0] * s[1], s[0] * s[1] * s[1] + s[4], s[0] * s[1] * s[2],
+                  s[0] * s[1] * s[3], s[1] * (s[0] * E + s[4]), s[0] * s[1] * e])
+    i = 1.0 / (sR - sL)
+    H = [(sR * a - sL * b + sL * sR * (d - c)) * i for a, b, c, d in zip(*F, *U)]
+    um = [(sR * U[1][k] - sL * U[0][k] - (F[1][k] - F[0][k])) * i for k in (0, 1)]
+    H.append(um[1] / um[0])
+    return [torch.where(sL >= 0, a, torch.where(sR <= 0, b, h))
+            for a, b, h in zip(F[0] + [L[1]], F[1] + [R[1]], H)]
+
+
+def _update(lam, c, Fm, Fp, mx, hg):
+    rho, u, v1, v2, E, e, p = c
+    rn = rho - lam * (Fp[0] - Fm[0])
+    mu = rho * u - lam * (Fp[1] - Fm[1])
+    m1 = rho * v1 - lam * (Fp[2] - Fm[2])
+    m2 = rho * v2 - lam * (Fp[3] - Fm[3])
+    mE = rho * E - lam * (Fp[4] - Fm[4])
+    me = rho * e - lam * (Fp[5] - Fm[5]) - lam * p * (Fp[6] - Fm[6])
+    if hg is not None:
+        mu = mu + hg * (rho + rn)
+        mE = mE + hg * (rho * u + mu)
+    ir = 1.0 / rn
+    un, v1n, v2n, En, er = mu * ir, m1 * ir, m2 * ir, mE * ir, me * ir
+    eps = En - 0.5 * (un * un + v1n * v1n + v2n * v2n)
+    sel = torch.where(_ratio_above(eps, En, ETA1), eps, er)
+    bad = ~(rn > FLOOR) | ~(sel > 0)
+    en = torch.where(_ratio_above(rn * eps, mx, ETA2), eps, er.clamp(min=E_FLOOR))
+    return [rn, un, v1n, v2n, En, en], bad
+
+
+def _sweep(f, reg, acc, axis, mask, g, dt, dx, a, case):
+    """One sweep of a stack of equal patches, in place (dt, dx: per patch)."""
+    dim = 3 - axis
+    trans = [t for t in (0, 1, 2) if t != axis]
+    names = ("rho", ("vx", "vy", "vz")[axis], *(("vx", "vy", "vz")[t] for t in trans), "etot",
+             "eint")
+    N = [f["rho"].shape[3 - t] for t in (0, 1, 2)]
+    block = [slice(None)] * 4
+    for t in trans:
+        if mask >> t & 1:
+            block[3 - t] = slice(g, N[t] - g)
+    outer = 3 - trans[1]                                   # slabs bound the temporaries
+    lo, hi, _ = block[outer].indices(f["rho"].shape[outer])
+    per = f["rho"][tuple(block)].numel() // (hi - lo)
+    slab = max(1, (1 << 25) // per)
+    lam = (dt / (a * dx)).view(-1, 1, 1, 1)
+    for z in range(lo, hi, slab):
+        at = list(block)
+        at[outer] = slice(z, min(hi, z + slab))
+        view = [f[k][tuple(at)].movedim(dim, -1) for k in names]
+        new, flux = _pencils([v.contiguous() for v in view], g, lam,
+                             None if acc is None else acc[axis][tuple(at)].movedim(dim, -1),
+                             (0.5 * dt / a).view(-1, 1, 1, 1), case)
+        for v, x in zip(view, new):
+            v[..., g:-g] = x
+        if reg is not None:
+            # (patch, t2, t1, face) restricted to the active pencils of this slab
+            i1 = slice(0, None) if mask >> trans[0] & 1 else slice(g, N[trans[0]] - g)
+            z0, z1 = max(z, g), min(z + slab, hi, N[trans[1]] - g)
+            if z1 <= z0:
+                continue
+            sizes = [N[t] - 2 * g for t in (0, 1, 2)]
+            areas = [sizes[1] * sizes[2], sizes[0] * sizes[2], sizes[0] * sizes[1]]
+            off = 12 * sum(areas[:axis])
+            lab = (0, 1 + axis, 1 + trans[0], 1 + trans[1], 4, 5)
+            for side, j in ((0, 0), (1, -1)):
+                face = reg[:, off + side * 6 * areas[axis]: off + (side + 1) * 6 * areas[axis]]
+                face = face.view(-1, 6, sizes[trans[1]], sizes[trans[0]])
+                for k in range(6):
+                    x = flux[k][..., j][:, z0 - z:z1 - z, i1]
+                    face[:, lab[k], z0 - g:z1 - g] = dt.view(-1, 1, 1) * x
+
+
+def _pencils(c, g, lam, acc, hgdt, case):
+    """New active cells and the face fluxes of pencils c = (rho, u, v1, v2, E,
+    e), each (..., n)."""
+    rho, u, v1, v2, E, e = c
+    n = rho.shape[-1]
+    p = _pressure(rho, u, v1, v2, E, e)
+    cs = torch.sqrt(GAMMA * p / rho)
+    par = _parabolas((rho, u, v1, v2, p))
+    # faces j+1/2, j = g-1 .. n-g-1; cell j of the parabolas is index j-2
+    m = n - 2 * g + 1
+    cells = [slice(g - 3 + s, g - 3 + s + m) for s in (0, 1)]
+    core = [slice(g - 1 + s, g - 1 + s + m) for s in (0, 1)]
+    L = _trace([[x[..., cells[0]] for x in q] for q in par], u[..., core[0]], cs[..., core[0]],
+               lam, True)
+    R = _trace([[x[..., cells[1]] for x in q] for q in par], u[..., core[1]], cs[..., core[1]],
+               lam, False)
+    del par
+
+    def diffuse(F):
+        if not case.get("diffusion"):
+            return F
+        a, b = ([x[..., s] for x in c] for s in core)
+        nu = 0.1 * (a[1] - b[1]).clamp(min=0)
+        ql, qr = ([x[0]] + [x[0] * y for y in x[1:]] for x in (a, b))
+        return [x + nu * (y - w) for x, y, w in zip(F, ql, qr)] + [F[6]]
+
+    F = diffuse(_hllc(L, R) if case.get("solver") == "hllc" else _two_shock(L, R))
+    act = slice(g, n - g)
+    cell = [x[..., act] for x in c] + [p[..., act]]
+    rE = rho * E
+    mx = torch.maximum(torch.maximum(rE[..., g - 1:n - g - 1], rE[..., act]),
+                       rE[..., g + 1:n - g + 1])
+    hg = None if acc is None else hgdt * acc[..., act].double()
+    new, bad = _update(lam, cell, [x[..., :-1] for x in F], [x[..., 1:] for x in F], mx, hg)
+    if bool(bad.any()):
+        hit = torch.zeros_like(F[0], dtype=torch.bool)
+        hit[..., :-1] |= bad
+        hit[..., 1:] |= bad
+        F = [torch.where(hit, h, x) for h, x in zip(diffuse(_hll(L, R)), F)]
+        new, bad = _update(lam, cell, [x[..., :-1] for x in F], [x[..., 1:] for x in F], mx, hg)
+        thin = bad & ~(new[0] > FLOOR)
+        new[0] = torch.where(thin, torch.full_like(new[0], FLOOR), new[0])
+        for k in (1, 2, 3):
+            new[k] = torch.where(thin, cell[k], new[k])
+        eps = FLOOR / ((GAMMA - 1.0) * new[0])
+        new[5] = torch.where(bad, eps, new[5])
+        new[4] = torch.where(bad, eps + 0.5 * (new[1] * new[1] + new[2] * new[2]
+                                               + new[3] * new[3]), new[4])
+    return new, F
+
+
+def _periodic(f, g):
+    for x in f.values():
+        for d in (3, 2, 1):
+            n = x.shape[d] - 2 * g
+            i = (torch.arange(n + 2 * g, device=x.device) - g) % n + g
+            for k in list(range(g)) + list(range(n + g, n + 2 * g)):
+                x.select(d, k).copy_(x.select(d, int(i[k])))
+
+
+def exact(case, seed):
+    if case["kind"] == "amr":
+        return None  # hundreds of patches over many substeps, each a launch per operation
+    if case["kind"] in ("grid", "noalloc"):
+        f, acc = _single(case, seed)
+        g, a = case["ghost"], EXPANSION[0] if case["sources"] else 1.0
+        f = {k: f[k].double()[None] for k in FIELDS}
+        acc = None if acc is None else [x[None] for x in acc]
+        dx = torch.tensor([1.0 / max(case["nx"], case["ny"], case["nz"])], dtype=torch.float64,
+                          device="cuda")
+        dt = _signal_dt(f, g, dx, a)
+        if case["sources"]:
+            H, i = EXPANSION[1] / a, (slice(None),) + (slice(g, -g),) * 3
+            for k in FIELDS[1:]:
+                x = {"etot": H * dt, "eint": 1.5 * (GAMMA - 1.0) * H * dt}.get(k, 0.5 * H * dt)
+                f[k][i] *= (1.0 - x) / (1.0 + x)
+                if case["prec"] == "mixed" and k[0] == "v":
+                    f[k][i] = f[k][i].float().double()
+        _periodic(f, g)
+        for k, axis in enumerate(ORDERS[0]):
+            _sweep(f, None, acc, axis, (1 << axis) - 1, g, dt, dx, a, case)
+        return dict({k: x[0] for k, x in f.items()}, dt=_signal_dt(f, g, dx, a))
+    specs, g = _specs(case), 3
+    flat, offs, shapes = _flat([d for d, _, _ in specs], case["recipe"], seed, case["prec"])
+    flat = {k: x.double() for k, x in flat.items()}
+    rsz = [12 * (d[0] * d[1] + d[1] * d[2] + d[0] * d[2]) for d, _, _ in specs]
+    roff = [0]
+    for r in rsz:
+        roff.append(roff[-1] + r)
+    reg = torch.zeros(roff[-1], dtype=torch.float64, device="cuda")
+    groups = {}
+    for i, (d, _, _) in enumerate(specs):
+        groups.setdefault(d, []).append(i)
+    nlevels = 7 if case["kind"] == "batch" else 9
+    stacks, dt = {}, torch.full((nlevels,), math.inf, dtype=torch.float64, device="cuda")
+    level = torch.tensor([s[1] for s in specs], device="cuda")
+    width = torch.tensor([s[2] for s in specs], dtype=torch.float64, device="cuda")
+
+    def reduce(into):
+        for d, ids in groups.items():
+            into.scatter_reduce_(0, level[ids], _signal_dt(stacks[d], g, width[ids], 1.0), "amin")
+
+    for d, ids in groups.items():
+        stacks[d] = {k: torch.stack([flat[k][offs[i]:offs[i + 1]].view(shapes[i]) for i in ids])
+                     for k in FIELDS}
+        if case["kind"] == "hier" and ids[0] == 0:
+            root = {k: x[:1] for k, x in stacks[d].items()}
+            _periodic(root, g)
+    reduce(dt)
+    for d, ids in groups.items():
+        r = torch.zeros((len(ids), rsz[ids[0]]), dtype=torch.float64, device="cuda")
+        for axis in ORDERS[0]:
+            _sweep(stacks[d], r, None, axis, (1 << axis) - 1, g, dt[level[ids]], width[ids], 1.0,
+                   case)
+        for j, i in enumerate(ids):
+            reg[roff[i]:roff[i + 1]] = r[j]
+            for k in FIELDS:
+                flat[k][offs[i]:offs[i + 1]] = stacks[d][k][j].reshape(-1)
+    if case["kind"] == "batch":
+        dt = torch.full_like(dt, math.inf)
+        reduce(dt)
+    return dict(flat, flux_reg=reg, dt=dt)
