@@ -91,7 +91,8 @@ def draw(rng):
     if kind == "batch":
         return dict(kind=kind, npatch=round(math.exp(rng.uniform(math.log(3), math.log(4000)))),
                     layout=rng.randrange(10000), prec=prec, recipe=recipe,
-                    solver=rng.choice(("two-shock", "two-shock", "hllc")), tuned=rng.random() < 0.5, graph=rng.random() < 0.5)
+                    solver=rng.choice(("two-shock", "two-shock", "hllc")),
+                    tuned=rng.random() < 0.5, graph=rng.random() < 0.5)
     if kind == "hier":
         return dict(kind=kind, n=rng.randrange(64, 257), npatch=rng.randrange(30, 400),
                     layout=rng.randrange(10000), prec=prec, recipe=recipe)
