@@ -120,18 +120,18 @@ __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRe
     qp[k] = from_right(q[k]);
   }
   const double rEm = from_left(rE), rEp = from_right(rE);
-  const double m3 = vmax<double>(vmax<double>(rEm, rE), rEp);
+  const double m3 = nmax(nmax(rEm, rE), rEp);
 
   // ---- limited slopes (cells 1..n-2), density second difference
   T dm[5];
 #pragma unroll
-  for (int k = 0; k < 5; ++k) dm[k] = limited_slope<T>(qm[k], q[k], qp[k]);
+  for (int k = 0; k < 5; ++k) dm[k] = limited_slope2<T>(qm[k], q[k], qp[k]);
   const T d2 = second_diff<T>(qm[0], q[0], qp[0]);
 
   // ---- interface value at face j+1/2 (cells 1..n-3)
   T face[5];
 #pragma unroll
-  for (int k = 0; k < 5; ++k) face[k] = interface_value<T>(q[k], qp[k], dm[k], from_right(dm[k]));
+  for (int k = 0; k < 5; ++k) face[k] = interface_value(q[k], qp[k], dm[k], from_right(dm[k]));
 
   // ---- flattening indicator (cells 2..n-3, else zero)
   T ft = T(0);
@@ -152,14 +152,14 @@ __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRe
     const T dmm = from_left(dm[0]), dmp = from_right(dm[0]);
     T eta = steepen_eta<T>(gam, qm[0], qp[0], qm[4], qp[4], d2m, d2p);
     if (eta != T(0)) {
-      l[0] = mad<T>(l[0], T(1) - eta, mad<T>(T(0.5), dmm, qm[0]) * eta);
-      rr[0] = mad<T>(rr[0], T(1) - eta, mad<T>(T(-0.5), dmp, qp[0]) * eta);
+      l[0] = mad<T>(l[0], T(1) - eta, xfma(T(0.25), dmm, qm[0]) * eta);
+      rr[0] = mad<T>(rr[0], T(1) - eta, xfma(T(-0.25), dmp, qp[0]) * eta);
     }
   }
   if (flatten) {
     const T ftm = from_left(ft), ftp = from_right(ft);
     T fn = (qp[4] - qm[4] > T(0)) ? ftm : ftp;
-    T f = vmax<T>(ft, fn);
+    T f = nmax(ft, fn);
     if (f != T(0)) {
 #pragma unroll
       for (int k = 0; k < 5; ++k) {
@@ -173,8 +173,8 @@ __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRe
   const T rho_floor = T(P.rho_floor), p_floor = T(P.p_floor);
   // left state of face j+1/2 (from this cell) and right state of face
   // (j-1)+1/2 (from this cell); face j+1/2 takes its right state from lane j+1
-  const State<T> sl = trace_edge<T, true>(gam, l, rr, dq, q6, q[1], cc, tlam, rho_floor, p_floor);
-  const State<T> srown = trace_edge<T, false>(gam, l, rr, dq, q6, q[1], cc, tlam, rho_floor, p_floor);
+  State<T> sl, srown;
+  trace_edges<T>(gam, l, rr, dq, q6, q[1], cc, tlam, rho_floor, p_floor, srown, sl);
   const State<T> sr = state_from_right(srown);
 
   // ---- Riemann problem at face j+1/2 (faces a0-1..a1), with the optional

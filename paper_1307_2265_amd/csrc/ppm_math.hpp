@@ -57,15 +57,33 @@ __device__ __forceinline__ double expansion_a(const Params &P, int level) {
 
 template <class T> __device__ __forceinline__ T vmin(T a, T b) { return a < b ? a : b; }
 template <class T> __device__ __forceinline__ T vmax(T a, T b) { return a > b ? a : b; }
+// Minimum and maximum as one instruction each (the ternary forms above cost a
+// compare and two selects per double); a NaN operand gives the other one.
+__device__ __forceinline__ double nmin(double a, double b) { return __builtin_fmin(a, b); }
+__device__ __forceinline__ float nmin(float a, float b) { return __builtin_fminf(a, b); }
+__device__ __forceinline__ double nmax(double a, double b) { return __builtin_fmax(a, b); }
+__device__ __forceinline__ float nmax(float a, float b) { return __builtin_fmaxf(a, b); }
 template <class T> __device__ __forceinline__ T clamp01(T x) {
-  return x < T(0) ? T(0) : (x > T(1) ? T(1) : x);
+  return nmin(nmax(x, T(0)), T(1));
+}
+__device__ __forceinline__ double csign(double a, double b) { return __builtin_copysign(a, b); }
+__device__ __forceinline__ float csign(float a, float b) { return __builtin_copysignf(a, b); }
+// a * b + c in one instruction, for products that are exact in themselves (a
+// a power of two, away from the subnormals): the same bits as the two
+// operations, one issue fewer.
+__device__ __forceinline__ double xfma(double a, double b, double c) { return fma(a, b, c); }
+__device__ __forceinline__ float xfma(float a, float b, float c) {
+  return __builtin_fmaf(a, b, c);
 }
 
 // Correctly rounded double quotient and square root for operands of
 // ordinary magnitude.  Both refine the hardware reciprocal (square root) by
-// Newton steps on fused multiply-adds and finish with one exact-remainder
-// correction, which yields the IEEE round-to-nearest result (Markstein's
-// theorem; the square root likewise).  They omit the operand scaling and
+// fused multiply-adds and finish with one exact-remainder correction, which
+// yields the IEEE round-to-nearest result (Markstein's theorem; the square
+// root likewise).  The reciprocal is refined by one cubic step, y (1 + e +
+// e^2) with e = 1 - b y: the hardware estimate carries about 24 correct bits,
+// so e^3 lies near 2^-70 and three fused operations do what two quadratic
+// steps take four for.  They omit the operand scaling and
 // special-value fix-ups that a general IEEE division or square root needs for
 // operands within 2^768 of the overflow or underflow threshold, zeros,
 // infinities and NaNs.  They serve only where the operands are bounded: the
@@ -76,16 +94,23 @@ template <class T> __device__ __forceinline__ T clamp01(T x) {
 // values; with state magnitudes below 1e100 every operand there is far inside
 // the range, and the results are bit for bit those of a / b and sqrt(x).  The
 // characteristic tracing, whose reconstructed edge values no floor bounds
-// (an edge density or pressure can be zero), uses xdiv / xsqrt instead.
-__device__ __forceinline__ double ddiv(double a, double b) {
-  double y = __builtin_amdgcn_rcp(b);
-  double e = fma(-b, y, 1.0);
-  y = fma(y, e, y);
-  e = fma(-b, y, 1.0);
-  y = fma(y, e, y);
+// (an edge density or pressure can be zero), uses xrcp / xsqrt instead.
+__device__ __forceinline__ double rcp_cubic(double b) {
+  const double y = __builtin_amdgcn_rcp(b);
+  const double e = fma(-b, y, 1.0);
+  return fma(y, fma(e, e, e), y);
+}
+// a / b from y, the correctly rounded (or, off in rare last bits, the cubic
+// step's) reciprocal of b.
+__device__ __forceinline__ double ddiv_by(double a, double b, double y) {
   const double q = a * y;
   const double r = fma(-b, q, a);
   return fma(r, y, q);
+}
+__device__ __forceinline__ double ddiv(double a, double b) { return ddiv_by(a, b, rcp_cubic(b)); }
+__device__ __forceinline__ double drcp(double b) {
+  const double y = rcp_cubic(b);
+  return fma(fma(-b, y, 1.0), y, y);
 }
 __device__ __forceinline__ double dsqrt(double x) {
   const double y = __builtin_amdgcn_rsq(x);
@@ -108,16 +133,23 @@ template <class T> __device__ __forceinline__ T rdiv(T a, T b) { return ddiv(a, 
 template <> __device__ __forceinline__ float rdiv<float>(float a, float b) {
   return a * __builtin_amdgcn_rcpf(b);
 }
-// IEEE quotient and square root for every operand (zeros, infinities and the
-// extreme exponents included), for the characteristic tracing; in the float
-// stages of the mixed precision the hardware reciprocal and square root.
-template <class T> __device__ __forceinline__ T xdiv(T a, T b) { return a / b; }
-template <> __device__ __forceinline__ float xdiv<float>(float a, float b) {
-  return a * __builtin_amdgcn_rcpf(b);
+// IEEE reciprocal and square root for the characteristic tracing, whose
+// operands may also be zero, negative, infinite or NaN: the sequences above
+// with the special operands put right, by v_div_fixup and by a select for a
+// zero root (a negative or NaN operand gives NaN by itself).  They leave out
+// only the scaling for extreme exponents: the reciprocal needs none for any
+// normal operand, and the root's operand (a product of two edge values, each
+// zero or at least an ulp of the 1e-100 floors) lies far above the 2^-900
+// below which its remainders would turn subnormal.  8 instructions instead of
+// 11, and 13 instead of 19.  In the float stages of the mixed precision the
+// hardware reciprocal.
+__device__ __forceinline__ double xrcp(double b) {
+  return __builtin_amdgcn_div_fixup(drcp(b), b, 1.0);
 }
-template <class T> __device__ __forceinline__ T xsqrt(T a) { return __builtin_sqrt(a); }
-template <> __device__ __forceinline__ float xsqrt<float>(float a) {
-  return __builtin_amdgcn_sqrtf(a);
+__device__ __forceinline__ float xrcp(float b) { return __builtin_amdgcn_rcpf(b); }
+__device__ __forceinline__ double xsqrt(double x) {
+  const double s = dsqrt(x);
+  return x == 0.0 ? x : s;
 }
 
 // a * b + c: in double two rounded operations, exactly the expression as
@@ -142,12 +174,9 @@ __device__ __forceinline__ bool ratio_above(double a, double b, double t) {
 __device__ __forceinline__ double eos_pressure(const Params &P, double rho, double u, double v1,
                                                double v2, double E, double e) {
   const double g = P.gamma;
-  double ke = 0.5 * (u * u + v1 * v1 + v2 * v2);
-  double eps = E - ke;
+  double eps = xfma(-0.5, u * u + v1 * v1 + v2 * v2, E);
   if ((P.flags & kDualEnergy) && !ratio_above(eps, E, P.eta1)) eps = e;
-  double pp = (g - 1.0) * rho * eps;
-  if (pp < P.p_floor) pp = P.p_floor;
-  return pp;
+  return nmax((g - 1.0) * rho * eps, P.p_floor);
 }
 __device__ __forceinline__ void eos(const Params &P, double rho, double u, double v1, double v2,
                                     double E, double e, double &p, double &c) {
@@ -171,28 +200,27 @@ __device__ __forceinline__ void eos_cell(const Params &P, double rho, double u, 
   }
 }
 
-// CW84 limited slope of a cell from its two neighbours.
-template <class T> __device__ __forceinline__ T limited_slope(T qm, T q0, T qp) {
-  T dl = q0 - qm, dr = qp - q0;
-  T dc = T(0.5) * (qp - qm);
-  T m = T(0);
-  if (dl * dr > T(0)) {
-    m = fabs(dc);
-    if (T(2) * fabs(dl) < m) m = T(2) * fabs(dl);
-    if (T(2) * fabs(dr) < m) m = T(2) * fabs(dr);
-    if (dc < T(0)) m = -m;
-  }
-  return m;
+// Twice the CW84 limited slope of a cell from its two neighbours (the doubling
+// is exact and spares the halving of the centred difference; the constants it
+// meets below are halved).
+template <class T> __device__ __forceinline__ T limited_slope2(T qm, T q0, T qp) {
+  const T dl = q0 - qm, dr = qp - q0, dc = qp - qm;
+  const T m = nmin(T(fabs(dc)), T(4) * nmin(T(fabs(dl)), T(fabs(dr))));
+  return dl * dr > T(0) ? csign(m, dc) : T(0);
 }
 
-// Fourth-order interface value between two cells from their limited slopes.
-template <class T> __device__ __forceinline__ T interface_value(T q0, T q1, T dm0, T dm1) {
-  return mad<T>(T(-kC16), dm1 - dm0, T(0.5) * (q0 + q1));
+// Fourth-order interface value between two cells from twice their limited
+// slopes.
+__device__ __forceinline__ double interface_value(double q0, double q1, double dm0, double dm1) {
+  return xfma(0.5, q0 + q1, (-0.5 * kC16) * (dm1 - dm0));
+}
+__device__ __forceinline__ float interface_value(float q0, float q1, float dm0, float dm1) {
+  return mad<float>(-0.5f * float(kC16), dm1 - dm0, 0.5f * (q0 + q1));
 }
 
 // Second difference of the density centred on a cell.
 template <class T> __device__ __forceinline__ T second_diff(T qm, T q0, T qp) {
-  return mad<T>(T(-2), q0, qp) + qm;
+  return xfma(T(-2), q0, qp) + qm;
 }
 
 // Contact-steepening weight eta of a cell (0 = no steepening).
@@ -200,10 +228,13 @@ template <class T> __device__ __forceinline__ T second_diff(T qm, T q0, T qp) {
 // differences centred on the two neighbours.
 template <class T>
 __device__ __forceinline__ T steepen_eta(double g, T rm, T rp, T pm, T pp, T d2m, T d2p) {
-  T drho = rp - rm;
+  const T drho = rp - rm;
+  const T rmin = nmin(rp, rm);
   T eta = T(0);
-  if (d2p * d2m < T(0) && fabs(drho) - T(kSteepEps) * vmin<T>(fabs(rp), fabs(rm)) > T(0) &&
-      T(g * kSteepK0) * fabs(drho) * vmin<T>(pp, pm) >= fabs(pp - pm) * vmin<T>(rp, rm)) {
+  const bool bend = d2p * d2m < T(0);
+  const bool jump = T(fabs(drho)) - T(kSteepEps) * rmin > T(0);
+  const bool contact = T(g * kSteepK0) * T(fabs(drho)) * nmin(pp, pm) >= T(fabs(pp - pm)) * rmin;
+  if (bend && jump && contact) {
     T etat = rdiv<T>(-(d2p - d2m), T(6) * drho);
     eta = clamp01<T>(T(kSteepEta1) * (etat - T(kSteepEta2)));
   }
@@ -214,41 +245,45 @@ __device__ __forceinline__ T steepen_eta(double g, T rm, T rp, T pm, T pp, T d2m
 // and the velocities of its neighbours.
 template <class T>
 __device__ __forceinline__ T flatten_indicator(T pm2, T pm1, T pp1, T pp2, T um1, T up1) {
-  T dp = pp1 - pm1;
+  const T dp = pp1 - pm1;
+  const bool shock = T(fabs(dp)) > T(kFlatEps) * nmin(pp1, pm1);
+  const bool converges = um1 - up1 > T(0);
   T f = T(0);
-  if (fabs(dp) > T(kFlatEps) * vmin<T>(pp1, pm1) && um1 - up1 > T(0)) {
-    T den = pp2 - pm2;
-    if (den == T(0)) f = T(1);
-    else f = clamp01<T>(T(kFlatOmega2) * (rdiv<T>(dp, den) - T(kFlatOmega1)));
+  if (shock && converges) {
+    const T den = pp2 - pm2;
+    const T v = clamp01<T>(T(kFlatOmega2) * (rdiv<T>(dp, den) - T(kFlatOmega1)));
+    f = den == T(0) ? T(1) : v;
   }
   return f;
 }
 
 // CW84 Eq. 1.10: make the parabola monotone, then return Delta q and q_6.
+// Written without branches: on any wave some lane takes each of them.
 template <class T> __device__ __forceinline__ void monotonize(T q, T &l, T &r, T &dq, T &q6) {
-  if ((r - q) * (q - l) <= T(0)) {
-    l = q;
-    r = q;
-  } else {
-    T d = r - l;
-    T s = d * mad<T>(T(-0.5), l + r, q);
-    T d2 = d * d * T(kC16);
-    if (s > d2) l = mad<T>(T(-2), r, T(3) * q);
-    else if (-d2 > s) r = mad<T>(T(-2), l, T(3) * q);
-  }
+  const bool flat = (r - q) * (q - l) <= T(0);
+  const T d = r - l;
+  const T s = d * xfma(T(-0.5), l + r, q);
+  const T d2 = d * d * T(kC16);
+  const T q3 = T(3) * q;
+  const T lo = s > d2 ? xfma(T(-2), r, q3) : l;
+  const T hi = -d2 > s ? xfma(T(-2), l, q3) : r;  // s > d2 >= 0 excludes it
+  l = flat ? q : lo;
+  r = flat ? q : hi;
   dq = r - l;
-  q6 = T(6) * mad<T>(T(-0.5), l + r, q);
+  q6 = T(6) * xfma(T(-0.5), l + r, q);
 }
 
-// Average of the parabola over the right-edge domain of a right-moving wave
-// of Courant number y, and over the left-edge domain of a left-moving one.
-template <class T> __device__ __forceinline__ T avg_right(T qr, T dq, T q6, T y) {
-  const T a = mad<T>(T(-kC23), y, T(1));
-  return mad<T>(-(T(0.5) * y), mad<T>(-a, q6, dq), qr);
+// Average of the parabola over the domain next to an edge that a wave of
+// Courant number |y| sweeps: the right edge for y >= 0, the left one for y <=
+// 0; w = 1 - 2/3 |y| with the sign of y (wave_weight).
+template <class T> __device__ __forceinline__ T wave_weight(T y) {
+  return mad<T>(T(-kC23), T(fabs(y)), T(1));
 }
-template <class T> __device__ __forceinline__ T avg_left(T ql, T dq, T q6, T y) {
-  const T a = mad<T>(T(-kC23), y, T(1));
-  return mad<T>(T(0.5) * y, mad<T>(a, q6, dq), ql);
+__device__ __forceinline__ double avg_edge(double edge, double dq, double q6, double y, double w) {
+  return xfma(-0.5, y * (dq - w * q6), edge);
+}
+__device__ __forceinline__ float avg_edge(float edge, float dq, float q6, float y, float w) {
+  return mad<float>(-(0.5f * y), mad<float>(-w, q6, dq), edge);
 }
 
 // A cell's parabola for the five reconstructed quantities.
@@ -261,83 +296,109 @@ template <class T> struct State {
   T r, u, v1, v2, p;
 };
 
-// CW84 characteristic tracing (Eqs. 3.5-3.7) of one cell edge.
-// RightEdge: the left state of the face to the right of the cell, built from
-// the waves moving right (u-c, u, u+c > 0); the reference state is the
-// average over the u+c domain, so the u+c correction vanishes whenever the
-// sound speed of the edge state is positive and finite; it is still formed as
-// the general formula writes it, which gives a NaN, not zero, when the edge
-// density or pressure is zero.  Left edge: the mirror image, with the u-c
-// domain as reference.
-// q: cell-centre u; c: sound speed; lam = dt/dx.
-template <class T, bool RightEdge>
-__device__ __forceinline__ State<T> trace_edge(double g, const T (&ql)[5], const T (&qrr)[5],
-                                               const T (&dq)[5], const T (&q6)[5], T u, T c,
-                                               T lam, T rho_floor, T p_floor) {
-  // quantity indices: 0 rho, 1 u, 2 v1, 3 v2, 4 p
-  State<T> s;
-  T yref, yslow, y0;
-  if (RightEdge) {
-    yslow = clamp01<T>((u - c) * lam);
-    y0 = clamp01<T>(u * lam);
-    yref = clamp01<T>((u + c) * lam);
-  } else {
-    yslow = clamp01<T>(-(u + c) * lam);
-    y0 = clamp01<T>(-u * lam);
-    yref = clamp01<T>(-(u - c) * lam);
-  }
-  auto avg = [&](int k, T y) -> T {
-    return RightEdge ? avg_right<T>(qrr[k], dq[k], q6[k], y) : avg_left<T>(ql[k], dq[k], q6[k], y);
-  };
-  T rt = avg(0, yref), ut = avg(1, yref), pt = avg(4, yref);
-  T C, iC, irt;
+// One edge's reference state: the averages of rho, u and p over the domain of
+// the fastest wave towards the face, and C = rho c, 1/C and 1/rho there.
+template <class T> struct EdgeRef {
+  T r, u, p, C, iC, ir;
+};
+template <class T>
+__device__ __forceinline__ EdgeRef<T> edge_ref(double g, const T (&edge)[5], const T (&dq)[5],
+                                               const T (&q6)[5], T y, T w) {
+  EdgeRef<T> e;
+  e.r = avg_edge(edge[0], dq[0], q6[0], y, w);
+  e.u = avg_edge(edge[1], dq[1], q6[1], y, w);
+  e.p = avg_edge(edge[4], dq[4], q6[4], y, w);
   if constexpr (sizeof(T) == sizeof(double)) {
-    C = xsqrt<T>(T(g) * pt * rt);
-    iC = xdiv<T>(T(1), C);
-    irt = xdiv<T>(T(1), rt);
+    e.C = xsqrt(T(g) * e.p * e.r);
+    e.iC = xrcp(e.C);
+    e.ir = xrcp(e.r);
   } else {
     // float: C = rho sqrt(g p / rho) and 1/C = (1/rho) / sqrt(g p / rho), so
     // that no product of two edge values (each as small as the floors, whose
     // product lies below the float range) is formed
-    irt = xdiv<T>(T(1), rt);
-    const T c2 = T(g) * pt * irt;
+    e.ir = xrcp(e.r);
+    const T c2 = T(g) * e.p * e.ir;
     const T ic = __builtin_amdgcn_rsqf(c2);
-    C = rt * (c2 * ic);
-    iC = irt * ic;
+    e.C = e.r * (c2 * ic);
+    e.iC = e.ir * ic;
   }
-  // bref: the reference wave's own correction (its averages are ut, pt);
-  // bslow: the other acoustic wave; b0: the entropy wave
-  T bref = T(0), bslow = T(0), b0 = T(0);
-  const bool ref_on = RightEdge ? (u + c > T(0)) : (u - c < T(0));
-  const bool slow_on = RightEdge ? (u - c > T(0)) : (u + c < T(0));
-  const bool zero_on = RightEdge ? (u > T(0)) : (u < T(0));
-  if (ref_on) {
-    if (RightEdge) bref = T(-0.5) * iC * ((ut - ut) + (pt - pt) * iC);        // beta-plus
-    else bref = T(0.5) * iC * ((ut - ut) - (pt - pt) * iC);                   // beta-minus
-  }
-  if (slow_on) {
-    T us = avg(1, yslow), ps = avg(4, yslow);
-    if (RightEdge) bslow = T(0.5) * iC * mad<T>(-(pt - ps), iC, ut - us);     // beta-minus
-    else bslow = T(-0.5) * iC * mad<T>(pt - ps, iC, ut - us);                  // beta-plus
-  }
-  if (zero_on) {
-    T r0 = avg(0, y0), p0 = avg(4, y0);
-    b0 = mad<T>((pt - p0) * iC, iC, irt) - xdiv<T>(T(1), r0);
-  }
-  T bp = RightEdge ? bref : bslow;
-  T bm = RightEdge ? bslow : bref;
+  return e;
+}
+// The edge's traced state from its reference state, the corrections bp, bm
+// (right- and left-moving acoustic wave) and b0 (entropy wave), and the
+// averaged transverse velocities.
+template <class T>
+__device__ __forceinline__ State<T> edge_state(const EdgeRef<T> &e, T bp, T bm, T b0, T v1, T v2,
+                                               T rho_floor, T p_floor) {
   T ps;
-  if constexpr (sizeof(T) == sizeof(double)) ps = mad<T>(C * C, bp + bm, pt);
-  else ps = mad<T>(C, C * (bp + bm), pt);  // C^2 alone can lie below the float range
-  T us = mad<T>(C, bp - bm, ut);
-  T tau = irt - (bp + bm + b0);
-  T rs = tau > T(0) ? xdiv<T>(T(1), tau) : rt;
-  s.r = vmax<T>(rs, rho_floor);
-  s.u = us;
-  s.p = vmax<T>(ps, p_floor);
-  s.v1 = avg(2, y0);
-  s.v2 = avg(3, y0);
-  return s;
+  if constexpr (sizeof(T) == sizeof(double)) ps = mad<T>(e.C * e.C, bp + bm, e.p);
+  else ps = mad<T>(e.C, e.C * (bp + bm), e.p);  // C^2 alone can lie below the float range
+  const T us = mad<T>(e.C, bp - bm, e.u);
+  const T tau = e.ir - (bp + bm + b0);
+  const T rs = tau > T(0) ? xrcp(tau) : e.r;
+  return State<T>{nmax(rs, rho_floor), us, v1, v2, nmax(ps, p_floor)};
+}
+
+// CW84 characteristic tracing (Eqs. 3.5-3.7) of both edges of a cell: `right`
+// gets the left state of the face to its right, built from the waves moving
+// right (u-c, u, u+c > 0), `left` the right state of the face to its left
+// from the waves moving left.  The reference state is the average over the
+// domain of the fastest wave (u+c, resp. u-c), so that wave's own correction
+// vanishes whenever the sound speed of the edge state is positive and finite;
+// it is still formed, as 1/C times a signed zero, which gives a NaN, not
+// zero, when the edge density or pressure is zero.
+// Only the edge the flow moves towards has an entropy wave (u > 0, resp. u <
+// 0) and, where |u| > c, a second acoustic one; towards the other edge their
+// Courant numbers are zero and their averages are the edge values.  So both
+// waves are evaluated once, for the side the sign of u picks, instead of once
+// per edge.  With the one-instruction minima and maxima, the branch-free
+// monotonizing and the shorter reciprocals the loop, which is bound by vector
+// issue, went from 2849 to 2523 instructions (512^3 step, FP64 27.1 -> 24.4
+// ms, mixed 17.4 -> 16.3 ms, bit for bit the same).
+// q: cell-centre u; c: sound speed; lam = dt/dx.
+template <class T>
+__device__ __forceinline__ void trace_edges(double g, const T (&l)[5], const T (&r)[5],
+                                            const T (&dq)[5], const T (&q6)[5], T u, T c, T lam,
+                                            T rho_floor, T p_floor, State<T> &left,
+                                            State<T> &right) {
+  // quantity indices: 0 rho, 1 u, 2 v1, 3 v2, 4 p; Courant numbers signed
+  // (negative towards the left edge)
+  const T up = u + c, um = u - c;
+  const T yr = nmin(nmax(up * lam, T(0)), T(1));
+  const T yl = nmin(nmax(um * lam, T(-1)), T(0));
+  const EdgeRef<T> er = edge_ref<T>(g, r, dq, q6, yr, wave_weight(yr));
+  const EdgeRef<T> el = edge_ref<T>(g, l, dq, q6, yl, -wave_weight(yl));
+  const bool pos = u > T(0), neg = u < T(0);
+  auto pick = [&](T a, T b) { return pos ? a : b; };
+  const T ref_p = pick(er.p, el.p), iC = pick(er.iC, el.iC), ir = pick(er.ir, el.ir);
+  // entropy wave and the transverse velocities it carries
+  const T y0 = nmin(nmax(u * lam, T(-1)), T(1));
+  const T w0 = csign(wave_weight(y0), u);
+  const T r0 = avg_edge(pick(r[0], l[0]), dq[0], q6[0], y0, w0);
+  const T v1 = avg_edge(pick(r[2], l[2]), dq[2], q6[2], y0, w0);
+  const T v2 = avg_edge(pick(r[3], l[3]), dq[3], q6[3], y0, w0);
+  const T ep = pick(r[4], l[4]);
+  const T p0 = avg_edge(ep, dq[4], q6[4], y0, w0);
+  const T b0 = mad<T>((ref_p - p0) * iC, iC, ir) - xrcp(r0);
+  // the acoustic wave against the flow, where it too moves downstream
+  T slow = T(0);
+  const T us = T(fabs(u)) - c;
+  if (us > T(0)) {
+    const T ys = csign(nmin(us * lam, T(1)), u);
+    const T ws = csign(wave_weight(ys), u);
+    const T du = pick(er.u, el.u) - avg_edge(pick(r[1], l[1]), dq[1], q6[1], ys, ws);
+    const T dp = ref_p - avg_edge(ep, dq[4], q6[4], ys, ws);
+    const T sg = pick(T(1), T(-1));
+    slow = T(0.5) * sg * iC * mad<T>(-sg * dp, iC, du);
+  }
+  const T zero = T(0);
+  const T sr = pos ? slow : zero, sl = neg ? slow : zero;
+  const T kr = up > T(0) ? -zero * er.iC : zero;  // the reference waves' own
+  const T kl = um < T(0) ? zero * el.iC : zero;
+  right = edge_state<T>(er, kr, sr, pos ? b0 : zero, pos ? v1 : r[2], pos ? v2 : r[3], rho_floor,
+                        p_floor);
+  left = edge_state<T>(el, sl, kl, neg ? b0 : zero, neg ? v1 : l[2], neg ? v2 : l[3], rho_floor,
+                       p_floor);
 }
 
 // Face flux in the flux type T of a precision: the mass and momentum fluxes
@@ -397,24 +458,24 @@ __device__ __forceinline__ StarState two_shock_star(const Params &P, double rl, 
   const double G1 = (g + 1.0) / (2.0 * g);
   double cl = dsqrt(g * pl * rl);
   double cr = dsqrt(g * pr * rr);
-  double ipl = ddiv(1.0, pl), ipr = ddiv(1.0, pr);
-  double ps = ddiv(cr * pl + cl * pr - cl * cr * (ur - ul), cl + cr);
-  if (ps < P.p_floor) ps = P.p_floor;
+  double ipl = drcp(pl), ipr = drcp(pr);
+  double ps = nmax(ddiv(cr * pl + cl * pr - cl * cr * (ur - ul), cl + cr), P.p_floor);
   int it = 0;
   bool capped = false;
   double wl, wr, iwl, iwr, usl, usr;
   for (;;) {
     wl = cl * dsqrt(1.0 + G1 * (ps * ipl - 1.0));
     wr = cr * dsqrt(1.0 + G1 * (ps * ipr - 1.0));
-    iwl = ddiv(1.0, wl);
-    iwr = ddiv(1.0, wr);
+    iwl = drcp(wl);
+    iwr = drcp(wr);
     usl = ul - (ps - pl) * iwl;
     usr = ur + (ps - pr) * iwr;
     if (capped || it == P.riemann_max_iter) break;
-    double izl = (wl * wl + cl * cl) * (0.5 * iwl * iwl * iwl);
-    double izr = (wr * wr + cr * cr) * (0.5 * iwr * iwr * iwr);
-    double pn = ps - ddiv(usr - usl, izl + izr);
-    if (pn < P.p_floor) pn = P.p_floor;
+    // twice 1/Z_s = (W_s^2 + C_s^2) / (2 W_s^3); the halving goes into the
+    // final fused subtraction, exactly
+    double izl = (wl * wl + cl * cl) * (iwl * iwl * iwl);
+    double izr = (wr * wr + cr * cr) * (iwr * iwr * iwr);
+    double pn = nmax(xfma(-2.0, ddiv(usr - usl, izl + izr), ps), P.p_floor);
     ++it;
     if (fabs(pn - ps) <= P.riemann_rtol * pn) break;
     ps = pn;
@@ -437,7 +498,8 @@ __device__ __forceinline__ Flux two_shock_flux(const Params &P, double rl, doubl
   const bool left = us >= 0.0;
   double rK = left ? rl : rr, uK = left ? ul : ur, pK = left ? pl : pr;
   double iwK = left ? iwl : iwr;
-  double rs = ddiv(1.0, ddiv(1.0, rK) - (ps - pK) * iwK * iwK);
+  const double irK = drcp(rK);
+  double rs = drcp(irK - (ps - pK) * iwK * iwK);
   if (rs < P.rho_floor) rs = P.rho_floor;
   // the upwind side's waves move away from the face: u - (speed) on the
   // left, u + (speed) on the right.  Written once with the side's values
@@ -448,12 +510,12 @@ __device__ __forceinline__ Flux two_shock_flux(const Params &P, double rl, doubl
   const double wK = left ? wl : wr;
   double rb, ub, pb;
   if (ps > pK) {  // shock on the upwind side
-    const double sK = uK + sgn * ddiv(wK, rK);
+    const double sK = uK + sgn * ddiv_by(wK, rK, irK);
     const bool keep = left ? sK >= 0.0 : sK <= 0.0;
     if (keep) { rb = rK; ub = uK; pb = pK; }
     else { rb = rs; ub = us; pb = ps; }
   } else {        // rarefaction: linear through the fan
-    const double head = uK + sgn * dsqrt(ddiv(g * pK, rK));
+    const double head = uK + sgn * dsqrt(ddiv_by(g * pK, rK, irK));
     const double tail = us + sgn * dsqrt(ddiv(g * ps, rs));
     bool outside = left ? head >= 0.0 : head <= 0.0;
     bool star = left ? tail <= 0.0 : tail >= 0.0;
@@ -475,7 +537,7 @@ __device__ __forceinline__ Flux two_shock_flux(const Params &P, double rl, doubl
   F.m[2] = fr * v1;
   F.m[3] = fr * v2;
   double eb = ddiv(pb, (g - 1.0) * rb);
-  double Eb = eb + 0.5 * (ub * ub + v1 * v1 + v2 * v2);
+  double Eb = xfma(0.5, ub * ub + v1 * v1 + v2 * v2, eb);
   F.E = fr * Eb + ub * pb;
   F.e = fr * eb;
   F.ub = ub;
@@ -536,12 +598,12 @@ __device__ __forceinline__ StarState two_shock_star_mixed(const Params &P, doubl
   // the same linear estimate with the impedances the shock relation gives as
   // p -> 0, W_s = k0 C_s, capped at that pressure.  Converges to the same
   // star pressure, in fewer steps on the wave's slowest faces.
-  const double pmin = pl < pr ? pl : pr;
+  const double pmin = nmin(pl, pr);
   if (ps < pmin) {
     const double ex = (cr * pl + cl * pr - P.shock_k0 * (cl * cr * (ur - ul))) * iden;
-    ps = ex < pmin ? ex : pmin;
+    ps = nmin(ex, pmin);
   }
-  if (ps < P.p_floor) ps = P.p_floor;
+  ps = nmax(ps, P.p_floor);
   int it = 0;
   bool capped = false;
   double wl, wr, iwl, iwr, usl, usr, yl, yr;
@@ -559,8 +621,7 @@ __device__ __forceinline__ StarState two_shock_star_mixed(const Params &P, doubl
     if (capped || it == P.riemann_max_iter) break;
     const double izl = fma(yl, yl, 1.0) * (0.5 * iwl);
     const double izr = fma(yr, yr, 1.0) * (0.5 * iwr);
-    double pn = fma(-(usr - usl), rcp64_1(izl + izr), ps);
-    if (pn < P.p_floor) pn = P.p_floor;
+    double pn = nmax(fma(-(usr - usl), rcp64_1(izl + izr), ps), P.p_floor);
     ++it;
     if (fabs(pn - ps) <= P.riemann_rtol * pn) break;
     ps = pn;
@@ -806,10 +867,9 @@ __device__ __forceinline__ bool update_cell(const Params &P, double lam, const C
     mu = mu + hg * (c.rho + rn);
     mE = mE + hg * (c.rho * c.u + mu);
   }
-  double ir = ddiv(1.0, rn);
+  double ir = drcp(rn);
   double un = mu * ir, v1n = m1 * ir, v2n = m2 * ir, En = mE * ir, eraw = me * ir;
-  double ke = 0.5 * (un * un + v1n * v1n + v2n * v2n);
-  double epsE = En - ke;
+  double epsE = xfma(-0.5, un * un + v1n * v1n + v2n * v2n, En);
   bool bad = !(rn > P.rho_floor);
   double sel = epsE;
   if (dual && !ratio_above(epsE, En, P.eta1)) sel = eraw;
@@ -850,8 +910,7 @@ __device__ __forceinline__ bool update_cell(const Params &P, double lam,
   const double ir = rcp64(rnd);
   const double un = unf, v1n = v1f, v2n = v2f;
   const double En = mE * ir, eraw = me * ir;
-  const double ke = 0.5 * (un * un + v1n * v1n + v2n * v2n);
-  const double epsE = En - ke;
+  const double epsE = xfma(-0.5, un * un + v1n * v1n + v2n * v2n, En);
   bool bad = !(rnd > P.rho_floor);
   double sel = epsE;
   if (dual && !ratio_above(epsE, En, P.eta1)) sel = eraw;

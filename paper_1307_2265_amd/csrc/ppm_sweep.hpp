@@ -280,7 +280,7 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
   T c_km1;
   double rE[3];    // cells k-2..k: rho*E of the sweep input
   double m3[5];    // cells k-5..k-1: max of rho*E over the cell and its neighbours
-  T dm[4][5];      // cells k-4..k-1: limited slopes
+  T dm[4][5];      // cells k-4..k-1: twice the limited slopes
   T d2[4];         // cells k-4..k-1: density second differences
   T ft[3];         // cells k-4..k-2: flattening indicators
   T fc[3][5];      // faces (k-4)+1/2 .. (k-2)+1/2: interface values
@@ -358,14 +358,14 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
     // ---- 2. slope and second difference of cell k-1, max rho*E around it
     if (t >= 2 && k <= n - 1) {
 #pragma unroll
-      for (int j = 0; j < 5; ++j) dm[3][j] = limited_slope<T>(q[2][j], q[3][j], q[4][j]);
+      for (int j = 0; j < 5; ++j) dm[3][j] = limited_slope2<T>(q[2][j], q[3][j], q[4][j]);
       d2[3] = second_diff<T>(q[2][0], q[3][0], q[4][0]);
-      m3[4] = vmax<double>(vmax<double>(rE[0], rE[1]), rE[2]);
+      m3[4] = nmax(nmax(rE[0], rE[1]), rE[2]);
     }
     // ---- 3. interface value between cells k-2 and k-1
     if (t >= 3 && k <= n - 1) {
 #pragma unroll
-      for (int j = 0; j < 5; ++j) fc[2][j] = interface_value<T>(q[2][j], q[3][j], dm[2][j], dm[3][j]);
+      for (int j = 0; j < 5; ++j) fc[2][j] = interface_value(q[2][j], q[3][j], dm[2][j], dm[3][j]);
     }
     // ---- 4. flattening indicator of cell k-2 (zero where its stencil leaves the pencil)
     ft[2] = T(0);
@@ -375,9 +375,9 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
     // ---- 5. parabola of cell r = k-3, traced to both edges
     const int r = k - 3;
     State<T> rstate = lcarry, lnew = lcarry;
-    const bool need_left_edge = r >= b0 && r <= a1 + 1;   // right state of face (r-1)+1/2
-    const bool need_right_edge = r >= b0 - 1 && r <= a1;  // left state of face r+1/2
-    if (need_left_edge || need_right_edge) {
+    // rstate: right state of face (r-1)+1/2 (used for r >= b0); lnew: left
+    // state of face r+1/2 (used for r <= a1)
+    if (r >= b0 - 1 && r <= a1 + 1) {
       T l[5], rr[5], dq[5], q6[5];
 #pragma unroll
       for (int j = 0; j < 5; ++j) {
@@ -387,13 +387,13 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
       if (steepen) {
         T eta = steepen_eta<T>(gam, q[0][0], q[2][0], q[0][4], q[2][4], d2[0], d2[2]);
         if (eta != T(0)) {
-          l[0] = mad<T>(l[0], T(1) - eta, mad<T>(T(0.5), dm[0][0], q[0][0]) * eta);
-          rr[0] = mad<T>(rr[0], T(1) - eta, mad<T>(T(-0.5), dm[2][0], q[2][0]) * eta);
+          l[0] = mad<T>(l[0], T(1) - eta, xfma(T(0.25), dm[0][0], q[0][0]) * eta);
+          rr[0] = mad<T>(rr[0], T(1) - eta, xfma(T(-0.25), dm[2][0], q[2][0]) * eta);
         }
       }
       if (flatten) {
         T fn = (q[2][4] - q[0][4] > T(0)) ? ft[0] : ft[2];
-        T f = vmax<T>(ft[1], fn);
+        T f = nmax(ft[1], fn);
         if (f != T(0)) {
 #pragma unroll
           for (int j = 0; j < 5; ++j) {
@@ -404,11 +404,7 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
       }
 #pragma unroll
       for (int j = 0; j < 5; ++j) monotonize<T>(q[1][j], l[j], rr[j], dq[j], q6[j]);
-      const T u = q[1][1], c = cw[0];
-      if (need_left_edge)
-        rstate = trace_edge<T, false>(gam, l, rr, dq, q6, u, c, tlam, rho_floor, p_floor);
-      if (need_right_edge)
-        lnew = trace_edge<T, true>(gam, l, rr, dq, q6, u, c, tlam, rho_floor, p_floor);
+      trace_edges<T>(gam, l, rr, dq, q6, q[1][1], cw[0], tlam, rho_floor, p_floor, rstate, lnew);
     }
 
     // ---- 6. Riemann problem at face fc = (r-1)+1/2
