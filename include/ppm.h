@@ -155,14 +155,15 @@ int64_t ppm_flux_reg_size(int32_t nx, int32_t ny, int32_t nz);
  * text of "key=value" pairs separated by spaces that overrides the launch
  * shapes; unknown keys are an error.  Keys:
  *   lanes=M        axis bitmask: sweeps along axis a (bit a) give each pencil
- *                  to a wavefront with its cells across the lanes (pencils of
- *                  at most 64 cells are packed side by side, 64/n per wave);
- *                  the other sweeps give each pencil to one thread that
- *                  marches it.  Default 1 (x only), except for one patch
- *                  with (nx + 2 ghost)(nz + 2 ghost) below 128 x the number
- *                  of compute units (too few pencils to fill the device one
- *                  thread each) and a tile_config that sets none of lanes,
- *                  block, tail and tail_round: then 7 (every axis).
+ *                  to a wavefront with its cells across the lanes (several
+ *                  pencils one after the other, in runs whose length fits the
+ *                  number of pencils and compute units); the other sweeps
+ *                  give each pencil to one thread that marches it.  Default 1
+ *                  (x only) and, unless tile_config sets one of lanes, block,
+ *                  tail and tail_round, the y and z axes too where the patches
+ *                  have too few pencils to fill the device one thread each:
+ *                  ghosted transverse pencils below 208 (y) and 160 (z) x the
+ *                  number of compute units for one patch, 416 for several.
  *   block=B        threads per block of the marching kernel (64..256;
  *                  default 256 for one patch, 64 for several).
  *   lanes_block=B  threads per block of the lane-parallel kernel (64..256;
@@ -177,8 +178,9 @@ int64_t ppm_flux_reg_size(int32_t nx, int32_t ny, int32_t nz);
  *                  sweeps back to back; with 0, one launch per sweep over all
  *                  patches.  A workgroup owns a whole patch, so persistent=1
  *                  needs every patch to hold at most 2^21 active cells
- *                  (PPM_EINVAL otherwise).  Default: 1 for several patches
- *                  that all satisfy this, else 0.
+ *                  (PPM_EINVAL otherwise).  Default 0 (the per-sweep launches
+ *                  were faster for every number of patches measured: 12
+ *                  patches 0.06 against 1.6 ms a step, 4096 7.4 against 8.4).
  *   batch_block=B  threads per workgroup of the persistent launch (64..256).
  *   batch_blocks=W workgroups of the persistent launch (default: 512/B per CU).
  *   tail=0|1       one ungrouped patch: when a marching sweep's pencils

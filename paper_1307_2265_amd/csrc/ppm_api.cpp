@@ -111,6 +111,72 @@ ppm::Params device_params(ppm_precision prec, const ppm_params *p) {
   return P;
 }
 
+int64_t sweep_pencils(const PatchDev &d, int axis, int tm) {
+  const int t1 = axis == 0 ? 1 : 0, t2 = axis == 2 ? 1 : 2;
+  const int64_t w1 = (tm & 1) ? d.n[t1] : d.n[t1] + 2 * d.ghost;
+  const int64_t w2 = (tm & 2) ? d.n[t2] : d.n[t2] + 2 * d.ghost;
+  return w1 * w2;
+}
+
+// Longer runs pack pencils more tightly into 64-lane segments, shorter ones
+// give the device more waves: the choice minimises the segments of a run (and
+// the start of a wave, 0.15 of one) times the waves per SIMD (at least 1.3,
+// where the latency of one wave's segments takes over, and half a wave more
+// than the mean for the uneven last round).  Over the FP64 cubes 16^3 .. 256^3
+// and the run lengths 1 .. 32 segments measured, the choice is within 9 % of
+// the best everywhere and the best or within 2 % of it on most (runs of 32
+// segments throughout took 16^3 484 us, 64^3 430 us and 128^3 1250 us a step;
+// these take 31, 121 and 480).  A y or z sweep over more data than half the
+// 256 MB of the last-level cache takes one pencil per wave: its waves share
+// lines of neighbouring pencils, which longer runs read again too late (192^3
+// y sweep 526 us with one, 655 with two).
+int32_t choose_run_segments(const PatchDev *d, int32_t npatch, ppm_precision prec, int axis,
+                            int tm, int cus) {
+  const double simds = 4.0 * (cus > 0 ? cus : 256);
+  int64_t cells = 0;
+  for (int32_t i = 0; i < npatch; ++i)
+    cells += sweep_pencils(d[i], axis, 0) * (d[i].n[axis] + 2 * d[i].ghost);
+  const int64_t bytes = cells * (prec == PPM_FP64 ? 48 : 32);
+  const int32_t most = axis != 0 && bytes > (int64_t(1) << 27) ? 1 : ppm::kMaxRunSegments;
+  int32_t best = 1;
+  double best_cost = std::numeric_limits<double>::infinity();
+  for (int32_t segs = 1; segs <= most; ++segs) {
+    double waves = 0.0, work = 0.0;
+    for (int32_t i = 0; i < npatch; ++i) {
+      const int n = d[i].n[axis] + 2 * d[i].ghost;
+      const int64_t np = sweep_pencils(d[i], axis, tm);
+      const int64_t rows = ppm::rows_per_wave(n, segs);
+      const double w = double((np + rows - 1) / rows);
+      waves += w;
+      work += w * (ppm::run_segments(int(std::min(rows, np) * n)) + 0.15);
+    }
+    const double cost = work / waves * std::max(1.3, waves / simds + 0.5);
+    if (cost < best_cost * 0.999) {
+      best_cost = cost;
+      best = segs;
+    }
+  }
+  return best;
+}
+
+// A marching sweep gives each pencil to one thread (two in a plan of one
+// patch), so with few pencils its time is that of one march whatever their
+// number, while a lane-parallel sweep's falls with them.  Measured, FP64
+// (mixed), us a sweep: 64^3 y 39 lane-parallel, 186 marching; 128^3 157 and
+// 345; 192^3 y 526 and 798 (359 and 525), z 746 and 796 (367 and 522); 224^3 y
+// 865 and 938, z 1536 and 936; 256^3 y 1305 and 1167 (853 and 788).  A z
+// sweep's lanes lie a plane apart, hence its earlier end.  Several patches of
+// 8^3 .. 32^3, us a step: 12 patches 62 and 328, 100 (60 thousand pencils a
+// sweep) 262 and 413 (193 and 317), 300 (180 thousand) 798 and 712.
+int32_t default_lanes(const PatchDev *d, int32_t npatch, int cus) {
+  int64_t np[2] = {0, 0};
+  for (int32_t i = 0; i < npatch; ++i)
+    for (int a = 0; a < 2; ++a) np[a] += sweep_pencils(d[i], a + 1, 0);
+  const int64_t c = cus;
+  return 1 | (np[0] < c * (npatch == 1 ? 208 : 416) ? 2 : 0) |
+         (np[1] < c * (npatch == 1 ? 160 : 416) ? 4 : 0);
+}
+
 }  // namespace ppm_detail
 
 using ppm_detail::fail;
@@ -215,7 +281,8 @@ hipError_t do_sweep(ppm_plan *pl, const double *dt, int axis, int mask, unsigned
     if (pl->nblocks[slot] == 0) return hipSuccess;
     return ppm::launch_sweep_lanes<Prec>(pl->d_patches, pl->d_chunks + slot * (pl->npatch + 1),
                                          pl->npatch, pl->nblocks[slot], pl->lanes_block, axis,
-                                         mask, dt, pl->P, pl->d_counters, smax, s);
+                                         mask, pl->lane_segs[axis * 4 + tm], dt, pl->P,
+                                         pl->d_counters, smax, s);
   }
   const int slot = axis * 4 + tm;
   if (pl->nblocks[slot] == 0) return hipSuccess;
@@ -289,10 +356,9 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
   int64_t max_cells = 0;
   for (int i = 0; i < npatch; ++i)
     max_cells = std::max(max_cells, int64_t(patches[i].nx) * patches[i].ny * patches[i].nz);
-  if (npatch > 1) {  // uneven patches: finer chunks, one persistent launch if they are small
+  if (npatch > 1) {  // uneven patches: finer chunks
     pl->block = 64;
     pl->lanes_block = 64;
-    pl->persistent = max_cells <= kPersistentMaxCells ? 1 : 0;
     pl->group = 1;
   }
   if ((st = parse_tiles(pl, tile_config)) != PPM_OK) {
@@ -309,20 +375,6 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
                 (long long)kPersistentMaxCells);
   }
   (void)hipGetDevice(&pl->device);
-  // One small patch: a marching sweep would give each of its few pencils a
-  // thread and leave most of the device idle (a 128^3 grid's y sweep has
-  // 134^2 pencils for 2 x 256 resident threads on each of 256 CUs), so every
-  // sweep streams its pencils through the lanes instead (measured: 128^3 FP64
-  // 1.80 -> 1.25 ms per step; from 192^3 on the marching sweeps are faster).
-  if (npatch == 1 && !pl->lanes_set) {
-    int cus0 = 0;
-    if (hipDeviceGetAttribute(&cus0, hipDeviceAttributeMultiprocessorCount, pl->device) !=
-        hipSuccess)
-      cus0 = 0;
-    const ppm_patch &q = patches[0];
-    const int64_t pencils = (int64_t(q.nx) + 2 * q.ghost) * (int64_t(q.nz) + 2 * q.ghost);
-    if (cus0 > 0 && pencils * 8 < int64_t(cus0) * 2 * 256 * 2) pl->lanes_mask = 7;
-  }
   pl->host.resize(npatch);
   pl->bc.resize(npatch);
   for (int i = 0; i < npatch; ++i) pl->bc[i] = patches[i].bc;
@@ -337,6 +389,10 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
     d.acc[0] = q.gx; d.acc[1] = q.gy; d.acc[2] = q.gz;
     if (q.gx) pl->P.flags |= ppm::kAnyGravity;
   }
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pl->device) != hipSuccess)
+    cus = 0;
+  if (!pl->lanes_set) pl->lanes_mask = ppm_detail::default_lanes(pl->host.data(), npatch, cus);
   // prefix arrays of work chunks
   const int stride = npatch + 1;
   std::vector<int32_t> chunks(size_t(25) * stride, 0);
@@ -346,16 +402,17 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
         const int slot = kind * 12 + axis * 4 + tm;
         int64_t acc = 0;
         int32_t *c = &chunks[size_t(slot) * stride];
-        const int t1 = t1_of(axis), t2 = t2_of(axis);
+        const bool used = (pl->lanes_mask >> axis) & 1;
+        const int32_t segs = kind == 1 && used
+            ? ppm_detail::choose_run_segments(pl->host.data(), npatch, prec, axis, tm, cus) : 1;
+        if (kind == 1) pl->lane_segs[axis * 4 + tm] = segs;
         for (int i = 0; i < npatch; ++i) {
           const PatchDev &d = pl->host[i];
-          const int64_t w1 = (tm & 1) ? d.n[t1] : d.n[t1] + 2 * d.ghost;
-          const int64_t w2 = (tm & 2) ? d.n[t2] : d.n[t2] + 2 * d.ghost;
           // work items: pencils (marching), or waves streaming runs of pencils
           // (lane-parallel)
-          int64_t items = w1 * w2, per_block = pl->block;
-          if (kind == 1) {  // a wave streams rows_per_wave(n) pencils
-            const int64_t rpw = ppm::rows_per_wave(int(d.n[axis] + 2 * d.ghost));
+          int64_t items = ppm_detail::sweep_pencils(d, axis, tm), per_block = pl->block;
+          if (kind == 1) {
+            const int64_t rpw = ppm::rows_per_wave(d.n[axis] + 2 * d.ghost, segs);
             items = (items + rpw - 1) / rpw;
             per_block = pl->lanes_block / 64;
           }
@@ -395,7 +452,6 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
     for (int axis = 0; axis < 3; ++axis)
       for (int tm = 0; tm < 4; ++tm) {
         const int slot = axis * 4 + tm;
-        const int t1 = t1_of(axis), t2 = t2_of(axis);
         std::vector<int32_t> sorted(npatch);
         for (int i = 0; i < npatch; ++i) sorted[i] = i;
         auto len = [&](int i) { return pl->host[i].n[axis] + 2 * pl->host[i].ghost; };
@@ -404,9 +460,7 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
         std::vector<int32_t> pp(size_t(npatch) + 1, 0), gfirst, gbs;
         int64_t acc = 0, blocks = 0;
         for (int j = 0; j < npatch; ++j) {
-          const PatchDev &d = pl->host[sorted[j]];
-          const int64_t w1 = (tm & 1) ? d.n[t1] : d.n[t1] + 2 * d.ghost;
-          const int64_t w2 = (tm & 2) ? d.n[t2] : d.n[t2] + 2 * d.ghost;
+          const int64_t np = ppm_detail::sweep_pencils(pl->host[sorted[j]], axis, tm);
           if (j == 0 || len(sorted[j]) != len(sorted[j - 1])) {
             if (j > 0) blocks += (acc - pp[gfirst.back()] + pl->block - 1) / pl->block;
             gfirst.push_back(j);
@@ -414,7 +468,7 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
           }
           runs_aligned = runs_aligned && aligned(sorted[j], sorted[gfirst.back()]);
           pp[j] = int32_t(acc);
-          acc += w1 * w2;
+          acc += np;
           if (acc > std::numeric_limits<int32_t>::max() / 2) {
             delete pl;
             return fail(PPM_EINVAL, "too many pencils for one launch");
@@ -454,18 +508,13 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
   // march a block more than the others (a 256^3 y sweep: 262 blocks of 256
   // on 256 compute units took 2.2 ms, the 256 blocks of its z sweep 1.55).
   // A given tail_round replaces the round and the eighth rule (any rest).
-  int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pl->device) != hipSuccess)
-    cus = 0;
   int64_t defer_pencils = 0;
   if (npatch == 1 && !pl->group && (cus > 0 || pl->tail_round > 0)) {
     for (int c = 0; c < 2; ++c) {
       for (int slot = 0; slot < 12; ++slot) {
         const int axis = slot / 4, tm = slot % 4;
         const PatchDev &d = pl->host[0];
-        const int64_t w1 = (tm & 1) ? d.n[t1_of(axis)] : d.n[t1_of(axis)] + 2 * d.ghost;
-        const int64_t w2 = (tm & 2) ? d.n[t2_of(axis)] : d.n[t2_of(axis)] + 2 * d.ghost;
-        const int64_t np = w1 * w2;
+        const int64_t np = ppm_detail::sweep_pencils(d, axis, tm);
         const bool split = pl->split && cus > 0 && d.n[axis] >= 16 &&
                            np < 2 * int64_t(cus) * pl->block;
         const int64_t tpp = split ? 2 : 1, threads = tpp * np;

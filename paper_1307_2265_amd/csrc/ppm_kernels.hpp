@@ -21,13 +21,14 @@ hipError_t launch_sweep(const PatchDev *patches, const int32_t *chunk_start, int
 // defer (nullable; a plan of one patch, no groups): sweep_split_kernel, two
 // threads per pencil, nblocks covering two threads per pencil, `defer` 30
 // doubles per pencil of workspace.
-// Lane-parallel variant (a wavefront streams a run of pencils); block = 64 * waves.
+// Lane-parallel variant (a wavefront streams a run of pencils of about `segs`
+// 64-lane segments); block = 64 * waves.
 // smax_bits (nullable) of a sweep launch: the sweep is the last of its step and
 // also takes the max signal speed per level of the cells it writes.
 template <class Prec>
 hipError_t launch_sweep_lanes(const PatchDev *patches, const int32_t *chunk_start, int32_t npatch,
                               int32_t nblocks, int32_t block, int32_t axis, int32_t mask,
-                              const double *dt_dev, const Params &P,
+                              int32_t segs, const double *dt_dev, const Params &P,
                               unsigned long long *counters, unsigned long long *smax_bits,
                               hipStream_t s);
 

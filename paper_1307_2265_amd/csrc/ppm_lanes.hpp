@@ -9,7 +9,9 @@
 // cell depends on the five cells either side of it in its own pencil (the
 // flattening of its neighbours' parabolas reaches three cells out, the HLL
 // fallback of a neighbouring face two more), so a segment writes its 54
-// middle cells and the 5 lanes at each end only supply halo values.
+// middle cells and the 5 lanes at each end only supply halo values (but for the
+// first lanes of a run's first segment and the last of its last, beyond which
+// no cell of the run lies).
 // Segments overlap by 10 cells; since the pencils are updated in place, the
 // next segment takes those cells' inputs from the registers of the previous
 // one (a lane permute) rather than from memory, where some were already
@@ -260,28 +262,28 @@ __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRe
   return F;
 }
 
-// One wave streams pencils first .. first+nrows-1 of a sweep's pencil set,
-// concatenated, segment by segment.
+// One wave streams the pencils first, first + step, ... (nrows of them) of a
+// sweep's pencil set, concatenated, segment by segment.
 // a: the patch level's expansion factor.
 template <class Prec, bool kCFL, bool kUseHLLC, bool kGrav>
 __device__ void sweep_rows_lanes(const Params &P, const PatchDev &pd, int axis, int mask,
-                                 int first, int nrows, double dt, double a, uint32_t &n_fallback,
-                                 uint32_t &n_floor, CflAcc &cfl) {
+                                 int first, int step, int nrows, double dt, double a,
+                                 uint32_t &n_fallback, uint32_t &n_floor, CflAcc &cfl) {
   using S = typename Prec::S;
   const int lane = threadIdx.x & 63;
   const int n = (axis == 0 ? pd.n[0] : (axis == 1 ? pd.n[1] : pd.n[2])) + 2 * pd.ghost;
   const int L = nrows * n;
-  const int nseg = (L + kLaneOut - 1) / kLaneOut;
+  const int nseg = run_segments(L);
   const double lam = dt / (a * pick3(axis, pd.dx[0], pd.dx[1], pd.dx[2]));
   const double hgdt = 0.5 * dt / a;
   CellLoad cur = {1.0, 0.0, 0.0, 0.0, 1.0, 1.0};
   for (int s = 0; s < nseg; ++s) {
-    const int t = s * kLaneOut - kLaneHalo + lane;  // stream position of this lane
-    const bool in = t >= 0 && t < L;
+    const int t = s * kLaneOut + lane;  // stream position of this lane
+    const bool in = t < L;
     const int row = in ? t / n : 0;
     const int j = in ? t - row * n : -1;
     int i1 = pd.ghost, i2 = pd.ghost;
-    pencil_index(pd, axis, mask, first + row, i1, i2);
+    pencil_index(pd, axis, mask, first + row * step, i1, i2);
     const PencilRef<S> pc = make_pencil<S>(pd, axis, i1, i2);
     // the first 2*halo lanes overlap the previous segment's last lanes
     CellLoad prev;
@@ -301,10 +303,14 @@ __device__ void sweep_rows_lanes(const Params &P, const PatchDev &pd, int axis, 
     } else {
       cur = CellLoad{1.0, 0.0, 0.0, 0.0, 1.0, 1.0};
     }
-    const bool mine = in && lane >= kLaneHalo && lane < kLaneHalo + kLaneOut;
+    // the lanes that write: all but the halo, which a run's ends do without
+    // (its first cells are ghosts, and past its last there is nothing to read)
+    const int lo = s == 0 ? 0 : kLaneHalo;
+    const int hi = s + 1 == nseg ? 64 : kLaneHalo + kLaneOut;
+    const bool mine = in && lane >= lo && lane < hi;
     // the written cells' faces, and the provisional fluxes of the faces one
     // further out that the fallback tests of the end cells read
-    const bool need_face = lane >= kLaneHalo - 2 && lane <= kLaneHalo + kLaneOut;
+    const bool need_face = lane >= lo - 2 && lane <= hi;
     sweep_segment<Prec, kCFL, kUseHLLC, kGrav>(P, pc, dt, lam, hgdt, j, mine, need_face, cur,
                                                n_fallback, n_floor, cfl);
   }

@@ -78,7 +78,8 @@ inline int t2_of(int axis) { return axis == 2 ? 1 : 2; }
 // default tile configuration, per-sweep launches (no persistent launch, no
 // grouped maps: each block belongs to one patch).
 struct Shapes {
-  int32_t block, lanes_block;
+  int32_t block, lanes_block, lanes_mask;
+  int32_t lane_segs[12];
   int32_t nblocks[kSlots];
   int32_t tail_pencil0[2][12], tail_main[2][12], tail_blocks[2][12];
 };
@@ -88,12 +89,12 @@ hipError_t sweep(const Shapes &sh, const PatchDev *patches, const int32_t *chunk
                  int axis, int mask, const double *dt, const ppm::Params &P,
                  unsigned long long *counters, unsigned long long *smax, hipStream_t s) {
   const int tm = ((mask >> t1_of(axis)) & 1) | (((mask >> t2_of(axis)) & 1) << 1);
-  if (axis == 0) {  // x sweeps: cells across the lanes
-    const int slot = 12 + tm;
+  if ((sh.lanes_mask >> axis) & 1) {  // cells across the lanes
+    const int slot = 12 + axis * 4 + tm;
     if (sh.nblocks[slot] == 0) return hipSuccess;
     return ppm::launch_sweep_lanes<Prec>(patches, chunks + slot * kStride, npatch,
-                                         sh.nblocks[slot], sh.lanes_block, axis, mask, dt, P,
-                                         counters, smax, s);
+                                         sh.nblocks[slot], sh.lanes_block, axis, mask,
+                                         sh.lane_segs[axis * 4 + tm], dt, P, counters, smax, s);
   }
   const int slot = axis * 4 + tm, c = smax ? 1 : 0;
   const int32_t *cs = chunks + slot * kStride;
@@ -189,6 +190,11 @@ extern "C" ppm_status ppm_step_cfl_noalloc(const ppm_patch *patches, int32_t npa
   std::memset(&sh, 0, sizeof sh);
   sh.block = npatch == 1 ? 256 : 64;
   sh.lanes_block = npatch == 1 ? 256 : 64;
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    cus = 0;
+  sh.lanes_mask = ppm_detail::default_lanes(host, npatch, cus);
   int32_t chunks[kSlots * kStride];
   std::memset(chunks, 0, sizeof chunks);
   for (int kind = 0; kind < 2; ++kind)
@@ -196,13 +202,14 @@ extern "C" ppm_status ppm_step_cfl_noalloc(const ppm_patch *patches, int32_t npa
       for (int tm = 0; tm < 4; ++tm) {
         const int slot = kind * 12 + axis * 4 + tm;
         int64_t acc = 0;
+        const int32_t segs = kind == 1 && ((sh.lanes_mask >> axis) & 1)
+            ? ppm_detail::choose_run_segments(host, npatch, prec, axis, tm, cus) : 1;
+        if (kind == 1) sh.lane_segs[axis * 4 + tm] = segs;
         for (int i = 0; i < npatch; ++i) {
           const PatchDev &d = host[i];
-          const int64_t w1 = (tm & 1) ? d.n[t1_of(axis)] : d.n[t1_of(axis)] + 2 * d.ghost;
-          const int64_t w2 = (tm & 2) ? d.n[t2_of(axis)] : d.n[t2_of(axis)] + 2 * d.ghost;
-          int64_t items = w1 * w2, per_block = sh.block;
+          int64_t items = ppm_detail::sweep_pencils(d, axis, tm), per_block = sh.block;
           if (kind == 1) {
-            const int64_t rpw = ppm::rows_per_wave(int(d.n[axis] + 2 * d.ghost));
+            const int64_t rpw = ppm::rows_per_wave(d.n[axis] + 2 * d.ghost, segs);
             items = (items + rpw - 1) / rpw;
             per_block = sh.lanes_block / 64;
           }
@@ -228,20 +235,13 @@ extern "C" ppm_status ppm_step_cfl_noalloc(const ppm_patch *patches, int32_t npa
   // one patch: whole rounds of one marching block per compute unit, the few
   // pencils left over to the lane-parallel tail launch (as a one-patch plan
   // does)
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    cus = 0;
   if (npatch == 1 && cus > 0)
     for (int c = 0; c < 2; ++c) {
       const int64_t cap = int64_t(cus) * sh.block;
       if (cap <= 0) continue;
       for (int slot = 0; slot < 12; ++slot) {
         const int axis = slot / 4, tm = slot % 4;
-        const PatchDev &d = host[0];
-        const int64_t w1 = (tm & 1) ? d.n[t1_of(axis)] : d.n[t1_of(axis)] + 2 * d.ghost;
-        const int64_t w2 = (tm & 2) ? d.n[t2_of(axis)] : d.n[t2_of(axis)] + 2 * d.ghost;
-        const int64_t np = w1 * w2, rest = np % cap;
+        const int64_t np = ppm_detail::sweep_pencils(host[0], axis, tm), rest = np % cap;
         if (np < cap || rest == 0 || rest * 8 > cap) continue;
         sh.tail_pencil0[c][slot] = int32_t(np - rest);
         sh.tail_main[c][slot] = int32_t((np - rest) / sh.block);

@@ -21,6 +21,7 @@ struct ppm_plan {
   int32_t lanes_block = 256;      // threads per lane-parallel block (64 per pencil)
   int32_t lanes_mask = 1;         // bit a: sweeps along axis a use the lane-parallel kernel
   bool lanes_set = false;         // lanes, or a marching-sweep shape, given in the tile config
+  int32_t lane_segs[12] = {};     // segments per run of each lane-parallel sweep
   int32_t cfl_cells = 4096;       // active cells per CFL block
   int32_t persistent = 0;         // ppm_step as one persistent launch over all patches
   int32_t batch_block = 256;      // threads per workgroup of the persistent kernel
@@ -77,6 +78,16 @@ double float_at_or_above(double x);
 // The device parameters of a precision (PPM_MIXED floors raised to floats;
 // no expansion factors).
 ppm::Params device_params(ppm_precision prec, const ppm_params *p);
+
+// Transverse pencils of a sweep along `axis` of a patch, tm its extent mask
+// (bit 0: the first transverse axis restricted to its active range, bit 1:
+// the second).
+int64_t sweep_pencils(const PatchDev &d, int axis, int tm);
+// Segments per wave run of a lane-parallel sweep over the patches, and the
+// axes that a plan sweeps that way by default (a bitmask).
+int32_t choose_run_segments(const PatchDev *d, int32_t npatch, ppm_precision prec, int axis,
+                            int tm, int cus);
+int32_t default_lanes(const PatchDev *d, int32_t npatch, int cus);
 
 // A box [lo, hi) of cell indices.
 struct IBox {

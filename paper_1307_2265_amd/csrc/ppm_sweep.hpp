@@ -75,13 +75,21 @@ constexpr int kLdsMarch = kLdsProvA + 6;
 constexpr int kLdsCfl = kLdsMarch;
 
 // Lane-parallel sweep: halo lanes at each end of a 64-lane segment, cells a
-// segment writes, and the pencils a wave streams in one run (about
-// kStreamCells cells).
+// segment writes, and the pencils of n cells a wave streams in one run of at
+// most `segs` segments (but always one pencil).  The ends of a run need no
+// halo, so s segments hold 54 s + 10 cells.
 constexpr int kLaneHalo = 5;
 constexpr int kLaneOut = 64 - 2 * kLaneHalo;
-constexpr int kStreamCells = 32 * kLaneOut;
-__host__ __device__ __forceinline__ int rows_per_wave(int n) {
-  return n >= kStreamCells ? 1 : (kStreamCells + n - 1) / n;
+constexpr int kMaxRunSegments = 32;
+__host__ __device__ __forceinline__ int rows_per_wave(int n, int segs) {
+  const int r = (segs * kLaneOut + 2 * kLaneHalo) / n;
+  return r > 1 ? r : 1;
+}
+// A patch's pencils go to its waves in groups of at most kDealWaves waves, a
+// group's in turn: wave w of G takes pencils w, w + G, ... of the group's.
+constexpr int kDealWaves = 128;
+__host__ __device__ __forceinline__ int run_segments(int cells) {
+  return cells <= 64 ? 1 : (cells - 2 * kLaneHalo + kLaneOut - 1) / kLaneOut;
 }
 
 // Select one of three values by a (wave-uniform) axis index without
