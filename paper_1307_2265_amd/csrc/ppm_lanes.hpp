@@ -224,8 +224,9 @@ __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRe
       if (diffuse) diffuse_into(H);
       if (hll) {
         F = H;
-        // face j+1/2 is counted by the wave that writes cell j (or cell a0 for the first face)
-        if (mine || (j == a0 - 1 && mine_next)) ++n_fallback;
+        // face j+1/2 is counted where cell j is written, the first face where cell a0 is (its
+        // own cell, a ghost, may lie in the segment before)
+        if (j == a0 - 1 ? mine_next : mine) ++n_fallback;
       }
       const bool hll_prev = from_left(int(hll)) != 0;
       Fm = flux_from_left(F);
