@@ -108,9 +108,7 @@ __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRe
   const bool has = j >= 0 && j < n;
   const int64_t o = pc.base + int64_t(has ? j : 0) * pc.stride;
   const double r = in.r, u = in.u, v1 = in.v1, v2 = in.v2, E = in.E, e = in.e;
-  double pd;
-  T cc;
-  eos_cell<T>(P, r, u, v1, v2, E, e, pd, cc);
+  const double pd = eos_pressure(P, r, u, v1, v2, E, e);
   T q[5] = {T(r), T(u), T(v1), T(v2), T(pd)};
   const double rE = r * E;
 
@@ -176,7 +174,7 @@ __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRe
   // left state of face j+1/2 (from this cell) and right state of face
   // (j-1)+1/2 (from this cell); face j+1/2 takes its right state from lane j+1
   State<T> sl, srown;
-  trace_edges<T>(gam, l, rr, dq, q6, q[1], cc, tlam, rho_floor, p_floor, srown, sl);
+  trace_edges<T>(gam, l, rr, dq, q6, q[1], sound_speed(gam, q[4], q[0]), tlam, rho_floor, p_floor, srown, sl);
   const State<T> sr = state_from_right(srown);
 
   // ---- Riemann problem at face j+1/2 (faces a0-1..a1), with the optional

@@ -180,24 +180,16 @@ __device__ __forceinline__ double eos_pressure(const Params &P, double rho, doub
 }
 __device__ __forceinline__ void eos(const Params &P, double rho, double u, double v1, double v2,
                                     double E, double e, double &p, double &c) {
-  const double pp = eos_pressure(P, rho, u, v1, v2, E, e);
-  p = pp;
-  c = dsqrt(ddiv(P.gamma * pp, rho));
+  p = eos_pressure(P, rho, u, v1, v2, E, e);
+  c = dsqrt(ddiv(P.gamma * p, rho));
 }
-// The pressure (double, from the selection rule) and the sound speed in the
-// reconstruction type T: for float, sqrt(g p / rho) with the float
-// reciprocal and square root (p / rho stays in range at the floors).
-template <class T>
-__device__ __forceinline__ void eos_cell(const Params &P, double rho, double u, double v1,
-                                         double v2, double E, double e, double &p, T &c) {
-  if constexpr (sizeof(T) == sizeof(double)) {
-    double cd;
-    eos(P, rho, u, v1, v2, E, e, p, cd);
-    c = cd;
-  } else {
-    p = eos_pressure(P, rho, u, v1, v2, E, e);
-    c = __builtin_amdgcn_sqrtf(float(P.gamma) * float(p) * __builtin_amdgcn_rcpf(float(rho)));
-  }
+// The sound speed in the reconstruction type: for float, sqrt(g p / rho) with
+// the float reciprocal and square root (p / rho stays in range at the floors).
+__device__ __forceinline__ double sound_speed(double g, double p, double rho) {
+  return dsqrt(ddiv(g * p, rho));
+}
+__device__ __forceinline__ float sound_speed(double g, float p, float rho) {
+  return __builtin_amdgcn_sqrtf(float(g) * p * __builtin_amdgcn_rcpf(rho));
 }
 
 // Twice the CW84 limited slope of a cell from its two neighbours (the doubling

@@ -5,9 +5,9 @@
 // of registers, so each input cell is read from HBM once and each updated cell
 // written once, with no LDS staging and no second pass.  With the head of the
 // walk at cell k:
-//   * cell k is loaded and its pressure and sound speed evaluated;
-//   * the limited slope of cell k-1 and the interface value between k-2 and
-//     k-1 are formed, and the flattening indicator of cell k-2;
+//   * cell k is loaded and its pressure evaluated;
+//   * the limited slope of cell k-2 and the interface value between k-3 and
+//     k-2 are formed, and the flattening indicator of cell k-2;
 //   * the parabola of cell r = k-3 is completed (steepening, flattening,
 //     monotonicity) and traced to both of its edges;
 //   * the Riemann problem at face (r-1)+1/2 is solved, giving the provisional
@@ -283,17 +283,21 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
   // Sliding windows; index 0 is the oldest cell.
   T q[5][5];       // cells k-4..k: rho, u, v1, v2, p
   double pd[5];    // cells k-4..k: pressure in double (update source term)
-  T cw[2];         // cells k-3 and k-2: sound speed (cw[0] is cell r)
-  T c_head;        // sound speed of the head cell
-  T c_km1;
   double rE[3];    // cells k-2..k: rho*E of the sweep input
   double m3[5];    // cells k-5..k-1: max of rho*E over the cell and its neighbours
-  T dm[4][5];      // cells k-4..k-1: twice the limited slopes
-  T d2[4];         // cells k-4..k-1: density second differences
+  T dm[3][5];      // cells k-4..k-2: twice the limited slopes
+  T d2[3];         // cells k-4..k-2: density second differences
   T ft[3];         // cells k-4..k-2: flattening indicators
-  T fc[3][5];      // faces (k-4)+1/2 .. (k-2)+1/2: interface values
+  T fc[2][5];      // faces (k-4)+1/2 and (k-3)+1/2: interface values
   State<T> lcarry; // left state of face r+1/2 from the previous iteration
+  State<T> rstate; // right state of face (r-1)+1/2
   FluxT<T> ft_b;   // two-shock flux at face (r-2)+1/2
+  FluxT<T> ft_c;   // and at face (r-1)+1/2
+  // provisional update of cell B = r-1, and its energies (and acceleration)
+  // as read ahead.  Like ft_c and rstate they keep their last value on the
+  // iterations that do not form them, none of which reads it (a reset would
+  // cost a move per value on every iteration).
+  double prov_b[6], EB, eB, gB;
   // final flux at face (r-3)+1/2 and provisional update of cell A = r-2 live
   // in LDS (written every step; the flux is read only by the fallback)
   double *ff_a = lds_slots + kLdsFluxA * slot_stride;
@@ -308,22 +312,20 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
     m3[i] = 0.0;
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < 3; ++i) {
 #pragma unroll
     for (int j = 0; j < 5; ++j) dm[i][j] = T(0);
     d2[i] = T(0);
-  }
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
     ft[i] = T(0);
     rE[i] = 0.0;
-#pragma unroll
-    for (int j = 0; j < 5; ++j) fc[i][j] = T(0);
   }
-  cw[0] = cw[1] = T(0);
-  c_head = c_km1 = T(0);
-  lcarry = State<T>{T(0), T(0), T(0), T(0), T(0)};
-  ft_b = zero_flux<T>();
+#pragma unroll
+  for (int j = 0; j < 5; ++j) fc[0][j] = fc[1][j] = T(0);
+  lcarry = rstate = State<T>{T(0), T(0), T(0), T(0), T(0)};
+  ft_b = ft_c = zero_flux<T>();
+#pragma unroll
+  for (int j = 0; j < 6; ++j) prov_b[j] = 0.0;
+  EB = eB = gB = 0.0;
 #pragma unroll
   for (int j = 0; j < 7; ++j) ff_a[j * slot_stride] = 0.0;
 #pragma unroll
@@ -340,7 +342,6 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
   for (int k = begin; k <= kend; ++k) {
     const int t = k - begin;  // cells read so far, less one
     // energies of cell B = k-4 (updated below), fetched early to hide latency
-    double EB = 0.0, eB = 0.0, gB = 0.0;
     if (k - 4 >= b0 && k - 4 <= a1) {
       const int64_t o = pc.base + int64_t(k - 4) * pc.stride;
       EB = pc.E[o];
@@ -355,25 +356,21 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
         const int64_t o = pc.base + int64_t(k + 1) * pc.stride;
         nr = pc.rho[o]; nu = pc.u[o]; nv1 = pc.v1[o]; nv2 = pc.v2[o]; nE = pc.E[o]; ne = pc.e[o];
       }
-      double p;
-      T c;
-      eos_cell<T>(P, r, u, v1, v2, E, e, p, c);
+      const double p = eos_pressure(P, r, u, v1, v2, E, e);
       q[4][0] = T(r); q[4][1] = T(u); q[4][2] = T(v1); q[4][3] = T(v2); q[4][4] = T(p);
       if (!kExactP) pd[4] = p;
-      c_head = c;
       rE[2] = r * E;
+      m3[4] = nmax(nmax(rE[0], rE[1]), rE[2]);  // of cell k-1
     }
-    // ---- 2. slope and second difference of cell k-1, max rho*E around it
-    if (t >= 2 && k <= n - 1) {
+    // ---- 2. slope and second difference of cell k-2, 3. interface value
+    // between cells k-3 and k-2 (as late as the parabola of cell k-3 allows:
+    // what is carried from one iteration to the next costs a move)
+    if (t >= 3 && k <= n) {
 #pragma unroll
-      for (int j = 0; j < 5; ++j) dm[3][j] = limited_slope2<T>(q[2][j], q[3][j], q[4][j]);
-      d2[3] = second_diff<T>(q[2][0], q[3][0], q[4][0]);
-      m3[4] = nmax(nmax(rE[0], rE[1]), rE[2]);
-    }
-    // ---- 3. interface value between cells k-2 and k-1
-    if (t >= 3 && k <= n - 1) {
+      for (int j = 0; j < 5; ++j) dm[2][j] = limited_slope2<T>(q[1][j], q[2][j], q[3][j]);
+      d2[2] = second_diff<T>(q[1][0], q[2][0], q[3][0]);
 #pragma unroll
-      for (int j = 0; j < 5; ++j) fc[2][j] = interface_value(q[2][j], q[3][j], dm[2][j], dm[3][j]);
+      for (int j = 0; j < 5; ++j) fc[1][j] = interface_value(q[1][j], q[2][j], dm[1][j], dm[2][j]);
     }
     // ---- 4. flattening indicator of cell k-2 (zero where its stencil leaves the pencil)
     ft[2] = T(0);
@@ -382,7 +379,7 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
 
     // ---- 5. parabola of cell r = k-3, traced to both edges
     const int r = k - 3;
-    State<T> rstate = lcarry, lnew = lcarry;
+    State<T> lnew = lcarry;
     // rstate: right state of face (r-1)+1/2 (used for r >= b0); lnew: left
     // state of face r+1/2 (used for r <= a1)
     if (r >= b0 - 1 && r <= a1 + 1) {
@@ -412,11 +409,10 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
       }
 #pragma unroll
       for (int j = 0; j < 5; ++j) monotonize<T>(q[1][j], l[j], rr[j], dq[j], q6[j]);
-      trace_edges<T>(gam, l, rr, dq, q6, q[1][1], cw[0], tlam, rho_floor, p_floor, rstate, lnew);
+      trace_edges<T>(gam, l, rr, dq, q6, q[1][1], sound_speed(gam, q[1][4], q[1][0]), tlam, rho_floor, p_floor, rstate, lnew);
     }
 
     // ---- 6. Riemann problem at face fc = (r-1)+1/2
-    FluxT<T> ft_c = zero_flux<T>();
     double *slot_c = lds_slots + (k & 1) * kSlotDoubles * slot_stride;
     if (r - 1 >= b0 - 1 && r - 1 <= a1) {
       ft_c = face_flux<kUseHLLC, T>(P, lcarry, rstate);
@@ -438,7 +434,6 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
     // ---- 7. provisional update of cell B = r-1 with the two-shock fluxes
     const int B = r - 1;
     bool bad_b = false;
-    double prov_b[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (B >= b0 && B <= a1) {
       CellInT<T> cin;
       cin.rho = q[0][0]; cin.u = q[0][1];
@@ -553,21 +548,15 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
       m3[i] = m3[i + 1];
     }
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < 2; ++i) {
 #pragma unroll
       for (int j = 0; j < 5; ++j) dm[i][j] = dm[i + 1][j];
       d2[i] = d2[i + 1];
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
       ft[i] = ft[i + 1];
       rE[i] = rE[i + 1];
-#pragma unroll
-      for (int j = 0; j < 5; ++j) fc[i][j] = fc[i + 1][j];
     }
-    cw[0] = cw[1];
-    cw[1] = c_km1;
-    c_km1 = c_head;
+#pragma unroll
+    for (int j = 0; j < 5; ++j) fc[0][j] = fc[1][j];
   }
 }
 
