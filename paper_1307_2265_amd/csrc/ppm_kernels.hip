@@ -33,6 +33,7 @@
 // mixed-precision marching sweeps, 3 the double-precision lane-parallel
 // sweeps (lanes and tail), 4 the mixed-precision lane-parallel ones; without
 // the macro one pass emits everything.
+#define PPM_KERNEL_SOURCE  // device code: see Dev in ppm_sweep.hpp
 #include "ppm_kernels.hpp"
 #include "ppm_lanes.hpp"
 
@@ -56,15 +57,6 @@ __device__ __forceinline__ int find_patch(const int32_t *start, int32_t npatch, 
   return lo;
 }
 
-// Fold a wave's signal-speed maxima into the level's device-wide max: a
-// wave-level max, then atomicMax on the bit pattern of the non-negative
-// double (which orders like the value).
-__device__ __forceinline__ void cfl_commit(double smax, unsigned long long *slot) {
-  smax = wave_max(smax);
-  if ((threadIdx.x & 63) == 0 && smax > 0.0)
-    atomicMax(slot, (unsigned long long)__double_as_longlong(smax));
-}
-
 // Largest i in [lo, hi) with a[i] <= x (a non-decreasing, a[lo] <= x).
 __device__ __forceinline__ int last_at_most(const int32_t *a, int lo, int hi, int32_t x) {
   while (hi - lo > 1) {
@@ -75,20 +67,11 @@ __device__ __forceinline__ int last_at_most(const int32_t *a, int lo, int hi, in
   return lo;
 }
 
-// Fold each lane's signal-speed maximum into its own level's maximum, for
-// waves whose lanes may belong to patches of different levels.
-__device__ __forceinline__ void cfl_commit_levels(double smax, int level,
-                                                  unsigned long long *smax_bits) {
-  const int lane = threadIdx.x & 63;
-  unsigned long long pending = __ballot(smax > 0.0);
-  while (pending) {
-    const int leader = __ffsll((long long)pending) - 1;
-    const int L = __shfl(level, leader, 64);
-    const bool take = smax > 0.0 && level == L;
-    const double m = wave_max(take ? smax : 0.0);
-    if (lane == leader) atomicMax(&smax_bits[L], (unsigned long long)__double_as_longlong(m));
-    pending &= ~__ballot(take);
-  }
+// Where a wave keeps the largest signal it knows of for a level, in the LDS
+// of a marching kernel.
+__device__ __forceinline__ unsigned long long *wave_top(double *lds, int level) {
+  return reinterpret_cast<unsigned long long *>(lds + kLdsCfl * int(blockDim.x) +
+                                                (int(threadIdx.x) & ~63) + level);
 }
 
 // One thread marches one pencil.  Ungrouped: each block takes `blockDim.x`
@@ -132,11 +115,11 @@ sweep_kernel(const PatchDev *__restrict__ patches, const int32_t *__restrict__ c
   const PatchDev pd = patches[p];
   int i1 = pd.ghost, i2 = pd.ghost;
   has = has && pencil_index(pd, axis, mask, idx, i1, i2);
-  if (!kCFL && !has) return;
-  CflAcc cfl = cfl_acc(pd, axis, lds + kLdsCfl * int(blockDim.x) + threadIdx.x);
-  if (kCFL) *cfl.lds = 0.0;
+  if (!has) return;
+  CflAcc cfl{};
+  if (kCFL) cfl = cfl_acc(&patches[p], axis, &smax_bits[pd.level], wave_top(lds, pd.level));
   uint32_t nfb = 0, nfl = 0;
-  if (has) {
+  {
     PencilRef<S> pc = make_pencil<S>(pd, axis, i1, i2);
     if (kGrouped) {
       // equal within a run of patches: keep the loop bounds scalar; address
@@ -155,10 +138,7 @@ sweep_kernel(const PatchDev *__restrict__ patches, const int32_t *__restrict__ c
   }
   if (nfb) atomicAdd(&counters[0], (unsigned long long)nfb);
   if (nfl) atomicAdd(&counters[1], (unsigned long long)nfl);
-  if (kCFL) {  // every lane of the wave takes part
-    if (kGrouped) cfl_commit_levels(*cfl.lds, pd.level, smax_bits);
-    else cfl_commit(*cfl.lds, &smax_bits[pd.level]);
-  }
+  if (kCFL) cfl_publish(cfl, pd.level);
 }
 
 // The marching sweep of one patch with two threads per pencil, for sweeps
@@ -183,11 +163,11 @@ sweep_split_kernel(const PatchDev *__restrict__ patches, int32_t axis, int32_t m
   const PatchDev pd = patches[0];
   int i1 = pd.ghost, i2 = pd.ghost;
   const bool has = pencil_index(pd, axis, mask, idx, i1, i2);
-  if (!kCFL && !has) return;
-  CflAcc cfl = cfl_acc(pd, axis, lds + kLdsCfl * int(blockDim.x) + threadIdx.x);
-  if (kCFL) *cfl.lds = 0.0;
+  if (!has) return;
+  CflAcc cfl{};
+  if (kCFL) cfl = cfl_acc(&patches[0], axis, &smax_bits[pd.level], wave_top(lds, pd.level));
   uint32_t nfb = 0, nfl = 0;
-  if (has) {
+  {
     const PencilRef<S> pc = make_pencil<S>(pd, axis, i1, i2);
     const double dt = dt_dev[pd.level];
     const int g = pc.g, a1 = pc.n - g - 1;
@@ -215,7 +195,7 @@ sweep_split_kernel(const PatchDev *__restrict__ patches, int32_t axis, int32_t m
   }
   if (nfb) atomicAdd(&counters[0], (unsigned long long)nfb);
   if (nfl) atomicAdd(&counters[1], (unsigned long long)nfl);
-  if (kCFL) cfl_commit(*cfl.lds, &smax_bits[pd.level]);  // every lane of the wave takes part
+  if (kCFL) cfl_publish(cfl, pd.level);
 }
 
 // Workgroups are dealt to the 8 XCDs in turn, each with an L2 of its own.
@@ -256,17 +236,24 @@ __device__ __forceinline__ void stream_pencils(const PatchDev *__restrict__ patc
   const int rows = (left - turn + G - 1) / G;
   const double dt = dt_dev[pd.level];
   uint32_t nfb = 0, nfl = 0;
-  CflAcc cfl = cfl_acc(pd, axis, nullptr);
+  __shared__ unsigned long long tops[kMaxBlock / 64];
+  CflAcc cfl{};
+  if (kCFL) cfl = cfl_acc(&patches[p], axis, &smax_bits[pd.level], &tops[threadIdx.x >> 6]);
   sweep_rows_lanes<Prec, kCFL, kUseHLLC, kGrav>(P, pd, axis, mask, pencil0 + begin + turn, G, rows,
                                                 dt, expansion_a(P, pd.level), nfb, nfl, cfl);
   if (nfb) atomicAdd(&counters[0], (unsigned long long)nfb);
   if (nfl) atomicAdd(&counters[1], (unsigned long long)nfl);
-  if (kCFL) cfl_commit(cfl.smax, &smax_bits[pd.level]);
+  if (kCFL) cfl_publish(cfl, pd.level);
 }
 
 // Lane-parallel sweep: each wavefront streams rows_per_wave(n, segs) pencils.
+// Four waves per SIMD; the builds that take the next timestep or carry the
+// gravity terms would spill there, and a reload that waits for the stores of
+// the segment before it costs more than the fourth wave gives (three waves:
+// mixed 512^3 last x sweep 5.62 -> 5.10 ms, FP64 8.43 -> 8.13, 128^3 with gravity
+// 181 -> 171 us; mixed without either 4.88 -> 4.98, hence four).
 template <class Prec, bool kCFL, bool kUseHLLC, bool kGrav>
-__global__ void __launch_bounds__(kMaxBlock, 4)
+__global__ void __launch_bounds__(kMaxBlock, kCFL || kGrav ? 3 : 4)
 sweep_lanes_kernel(const PatchDev *__restrict__ patches, const int32_t *__restrict__ chunk_start,
                    int32_t npatch, int32_t axis, int32_t mask, int32_t segs,
                    const double *__restrict__ dt_dev, Params P,
@@ -332,8 +319,10 @@ batch_persistent_kernel(const PatchDev *__restrict__ patches, const int32_t *__r
       const int w2 = ((mask >> t2) & 1) ? Nt2 : Nt2 + 2 * g;
       const int np = w1 * w2;
       int i1, i2;
-      CflAcc cfl = cfl_acc(pd, axis, lds + kLdsCfl * int(blockDim.x) + threadIdx.x);
-      if (kCFL && k == 2) *cfl.lds = 0.0;
+      CflAcc cfl{};
+      if (kCFL && k == 2)
+        cfl = cfl_acc(&patches[order[item]], axis, &smax_bits[pd.level],
+                      wave_top(lds, pd.level));
       if ((lanes_mask >> axis) & 1) {
         // the patch's pencils dealt to the waves in turn, one run per wave
         const int rows = (np - wave + waves - 1) / waves;
@@ -361,8 +350,7 @@ batch_persistent_kernel(const PatchDev *__restrict__ patches, const int32_t *__r
                                                        cfl);
         }
       }
-      if (kCFL && k == 2)
-        cfl_commit(((lanes_mask >> axis) & 1) ? cfl.smax : *cfl.lds, &smax_bits[pd.level]);
+      if (kCFL && k == 2) cfl_publish(cfl, pd.level);
       __syncthreads();  // this sweep of the patch is complete before the next reads it
       mask |= 1 << axis;
     }
@@ -397,10 +385,10 @@ cfl_reduce_kernel(const PatchDev *__restrict__ patches, const int32_t *__restric
   const int64_t nfx = nx + 2 * g, nfy = ny + 2 * g;
   const int64_t c0 = int64_t(blockIdx.x - chunk_start[p]) * cells_per_block;
   const int64_t c1 = c0 + cells_per_block < total ? c0 + cells_per_block : total;
-  const S *rho = static_cast<const S *>(pd.rho);
-  const S *vx = static_cast<const S *>(pd.vel[0]);
-  const S *vy = static_cast<const S *>(pd.vel[1]);
-  const S *vz = static_cast<const S *>(pd.vel[2]);
+  const Dev<const S> rho = dev<const S>(pd.rho);
+  const Dev<const S> vx = dev<const S>(pd.vel[0]);
+  const Dev<const S> vy = dev<const S>(pd.vel[1]);
+  const Dev<const S> vz = dev<const S>(pd.vel[2]);
   double smax = 0.0;
   for (int64_t c = c0 + threadIdx.x; c < c1; c += blockDim.x) {
     const int64_t x = c % nx, yz = c / nx;
@@ -463,9 +451,9 @@ expansion_kernel(const PatchDev *__restrict__ patches, const int32_t *__restrict
   const double fv = (1.0 - xv) / (1.0 + xv);
   const double fE = (1.0 - xE) / (1.0 + xE);
   const double fe = (1.0 - xe) / (1.0 + xe);
-  S *vx = static_cast<S *>(pd.vel[0]);
-  S *vy = static_cast<S *>(pd.vel[1]);
-  S *vz = static_cast<S *>(pd.vel[2]);
+  const Dev<S> vx = dev<S>(pd.vel[0]);
+  const Dev<S> vy = dev<S>(pd.vel[1]);
+  const Dev<S> vz = dev<S>(pd.vel[2]);
   for (int64_t c = c0 + threadIdx.x; c < c1; c += blockDim.x) {
     const int64_t x = c % nx, yz = c / nx;
     const int64_t y = yz % ny, z = yz / ny;
@@ -549,9 +537,9 @@ fill_boundary_kernel(PatchDev pd, FaceRules fr) {
       sc[a] = side == 0 ? g : g + N[a] - 1;
     }
   }
-  S *rho = static_cast<S *>(pd.rho);
-  S *vel[3] = {static_cast<S *>(pd.vel[0]), static_cast<S *>(pd.vel[1]),
-               static_cast<S *>(pd.vel[2])};
+  const Dev<S> rho = dev<S>(pd.rho);
+  const Dev<S> vel[3] = {dev<S>(pd.vel[0]), dev<S>(pd.vel[1]),
+               dev<S>(pd.vel[2])};
   const int64_t dst = (c[2] * nf[1] + c[1]) * nf[0] + c[0];
   S r, v[3];
   double E, e;
@@ -743,7 +731,7 @@ fill_from_parent_kernel(const PatchDev *__restrict__ patches, const InterpItem *
 #pragma unroll
   for (int a = 0; a < 3; ++a) lc[a] = cc[a] - item.pstart[a] + gc;
   const int64_t o0 = ((lc[2] - 1) * nc[1] + (lc[1] - 1)) * nc[0] + (lc[0] - 1);
-  const S *rho_c = static_cast<const S *>(cd.rho);
+  const Dev<const S> rho_c = dev<const S>(cd.rho);
   // the density of the neighbourhood, read once for all six quantities
   double rn[27];
   auto cell = [&](int dz, int dy, int dx) __attribute__((always_inline)) {
@@ -757,11 +745,11 @@ fill_from_parent_kernel(const PatchDev *__restrict__ patches, const InterpItem *
                     double &fz) __attribute__((always_inline)) {
     // (pointers picked by value, not by a run-time index into the table's
     // arrays, which would put the table in scratch memory)
-    const S *xs = comp == 1   ? static_cast<const S *>(cd.vel[0])
-                  : comp == 2 ? static_cast<const S *>(cd.vel[1])
-                  : comp == 3 ? static_cast<const S *>(cd.vel[2])
+    const Dev<const S> xs = comp == 1   ? dev<const S>(cd.vel[0])
+                         : comp == 2 ? dev<const S>(cd.vel[1])
+                  : comp == 3 ? dev<const S>(cd.vel[2])
                               : nullptr;
-    const double *xd = comp == 4 ? cd.etot : cd.eint;
+    const Dev<double> xd = comp == 4 ? cd.etot : cd.eint;
     CornerSums cs;
     corner_sums_begin(cs);
     auto value = [&](int m) __attribute__((always_inline)) {
@@ -785,9 +773,9 @@ fill_from_parent_kernel(const PatchDev *__restrict__ patches, const InterpItem *
   double q0[6], fx[6], fy[6], fz[6];
 #pragma unroll
   for (int comp = 0; comp < 6; ++comp) slopes(comp, q0[comp], fx[comp], fy[comp], fz[comp]);
-  S *rho_p = static_cast<S *>(fd.rho);
-  S *vel[3] = {static_cast<S *>(fd.vel[0]), static_cast<S *>(fd.vel[1]),
-               static_cast<S *>(fd.vel[2])};
+  const Dev<S> rho_p = dev<S>(fd.rho);
+  const Dev<S> vel[3] = {dev<S>(fd.vel[0]), dev<S>(fd.vel[1]),
+               dev<S>(fd.vel[2])};
   for (int k = 0; k < r; ++k)
     for (int j = 0; j < r; ++j)
       for (int i = 0; i < r; ++i) {
@@ -833,10 +821,10 @@ copy_from_siblings_kernel(const PatchDev *__restrict__ patches, const SiblingBox
   const int64_t sc[3] = {c[0] + box.shift[0], c[1] + box.shift[1], c[2] + box.shift[2]};
   const int64_t dst = (c[2] * nd[1] + c[1]) * nd[0] + c[0];
   const int64_t src = (sc[2] * ns[1] + sc[1]) * ns[0] + sc[0];
-  static_cast<S *>(dd.rho)[dst] = static_cast<const S *>(sd.rho)[src];
+  dev<S>(dd.rho)[dst] = dev<const S>(sd.rho)[src];
 #pragma unroll
   for (int a = 0; a < 3; ++a)
-    static_cast<S *>(dd.vel[a])[dst] = static_cast<const S *>(sd.vel[a])[src];
+    dev<S>(dd.vel[a])[dst] = dev<const S>(sd.vel[a])[src];
   dd.etot[dst] = sd.etot[src];
   dd.eint[dst] = sd.eint[src];
 }
@@ -887,7 +875,7 @@ capture_kernel(const PatchDev *__restrict__ patches, const CaptureRow *__restric
     cur.E = pc.E[o]; cur.e = pc.e[o];
   }
   uint32_t nfb = 0, nfl = 0;
-  CflAcc cfl = cfl_acc(pd, axis, nullptr);
+  const CflAcc cfl{};
   // the face's final flux reads the provisional fluxes of faces j-1/2 ..
   // j+3/2 (the fallback tests of cells j and j+1)
   const bool need_face = pos >= 3 && pos <= 5;
@@ -919,10 +907,10 @@ box_state_kernel(const PatchDev *__restrict__ cur_tab, const PatchDev *__restric
   const int64_t g = cd.ghost;
   const int64_t nx = cd.n[0] + 2 * g, ny = cd.n[1] + 2 * g;
   const int64_t o = (c[2] * ny + c[1]) * nx + c[0];
-  const S *cs[4] = {static_cast<const S *>(cd.rho), static_cast<const S *>(cd.vel[0]),
-                    static_cast<const S *>(cd.vel[1]), static_cast<const S *>(cd.vel[2])};
-  S *os[4] = {static_cast<S *>(od.rho), static_cast<S *>(od.vel[0]),
-              static_cast<S *>(od.vel[1]), static_cast<S *>(od.vel[2])};
+  const Dev<const S> cs[4] = {dev<const S>(cd.rho), dev<const S>(cd.vel[0]),
+                    dev<const S>(cd.vel[1]), dev<const S>(cd.vel[2])};
+  const Dev<S> os[4] = {dev<S>(od.rho), dev<S>(od.vel[0]),
+              dev<S>(od.vel[1]), dev<S>(od.vel[2])};
   if (!kBlend) {
 #pragma unroll
     for (int f = 0; f < 4; ++f) os[f][o] = cs[f][o];
@@ -931,8 +919,8 @@ box_state_kernel(const PatchDev *__restrict__ cur_tab, const PatchDev *__restric
     return;
   }
   const PatchDev md = mid_tab[box.patch];
-  S *ms[4] = {static_cast<S *>(md.rho), static_cast<S *>(md.vel[0]),
-              static_cast<S *>(md.vel[1]), static_cast<S *>(md.vel[2])};
+  const Dev<S> ms[4] = {dev<S>(md.rho), dev<S>(md.vel[0]),
+              dev<S>(md.vel[1]), dev<S>(md.vel[2])};
   const double wo = 1.0 - w;
 #pragma unroll
   for (int f = 0; f < 4; ++f) ms[f][o] = S(wo * double(os[f][o]) + w * double(cs[f][o]));
@@ -981,10 +969,10 @@ flux_correct_kernel(const PatchDev *__restrict__ patches, const CorrTarget *__re
     }
   }
   const int64_t o = tg.cell;
-  S *rho_p = static_cast<S *>(pd.rho);
-  S *vx = static_cast<S *>(pd.vel[0]);
-  S *vy = static_cast<S *>(pd.vel[1]);
-  S *vz = static_cast<S *>(pd.vel[2]);
+  const Dev<S> rho_p = dev<S>(pd.rho);
+  const Dev<S> vx = dev<S>(pd.vel[0]);
+  const Dev<S> vy = dev<S>(pd.vel[1]);
+  const Dev<S> vz = dev<S>(pd.vel[2]);
   const double rho = double(rho_p[o]);
   const double rn = rho + dq[0];
   const double mx = rho * double(vx[o]) + dq[1];
@@ -1020,9 +1008,9 @@ project_kernel(const PatchDev *__restrict__ patches, const ProjItem *__restrict_
   const int gc = cd.ghost, gf = fd.ghost, r = item.r;
   const int64_t nc[2] = {int64_t(cd.n[0]) + 2 * gc, int64_t(cd.n[1]) + 2 * gc};
   const int64_t nf[2] = {int64_t(fd.n[0]) + 2 * gf, int64_t(fd.n[1]) + 2 * gf};
-  const S *frho = static_cast<const S *>(fd.rho);
-  const S *fv[3] = {static_cast<const S *>(fd.vel[0]), static_cast<const S *>(fd.vel[1]),
-                    static_cast<const S *>(fd.vel[2])};
+  const Dev<const S> frho = dev<const S>(fd.rho);
+  const Dev<const S> fv[3] = {dev<const S>(fd.vel[0]), dev<const S>(fd.vel[1]),
+                    dev<const S>(fd.vel[2])};
   double s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   for (int kk = 0; kk < r; ++kk)
     for (int jj = 0; jj < r; ++jj)
@@ -1042,10 +1030,10 @@ project_kernel(const PatchDev *__restrict__ patches, const ProjItem *__restrict_
   const double vol = double(r * r * r);
   const int64_t o = ((z + gc) * nc[1] + (y + gc)) * nc[0] + (x + gc);
   const double rho = s[0] / vol;
-  static_cast<S *>(cd.rho)[o] = S(rho);
-  static_cast<S *>(cd.vel[0])[o] = S((s[1] / vol) / rho);
-  static_cast<S *>(cd.vel[1])[o] = S((s[2] / vol) / rho);
-  static_cast<S *>(cd.vel[2])[o] = S((s[3] / vol) / rho);
+  dev<S>(cd.rho)[o] = S(rho);
+  dev<S>(cd.vel[0])[o] = S((s[1] / vol) / rho);
+  dev<S>(cd.vel[1])[o] = S((s[2] / vol) / rho);
+  dev<S>(cd.vel[2])[o] = S((s[3] / vol) / rho);
   cd.etot[o] = (s[4] / vol) / rho;
   cd.eint[o] = (s[5] / vol) / rho;
 }
@@ -1068,10 +1056,10 @@ fill_periodic_kernel(PatchDev pd) {
   auto wrap = [&](int64_t i, int d) { return g + (((i - g) % N[d]) + N[d]) % N[d]; };
   const int64_t dst = (z * nf[1] + y) * nf[0] + x;
   const int64_t src = (wrap(z, 2) * nf[1] + wrap(y, 1)) * nf[0] + wrap(x, 0);
-  S *rho = static_cast<S *>(pd.rho);
-  S *vx = static_cast<S *>(pd.vel[0]);
-  S *vy = static_cast<S *>(pd.vel[1]);
-  S *vz = static_cast<S *>(pd.vel[2]);
+  const Dev<S> rho = dev<S>(pd.rho);
+  const Dev<S> vx = dev<S>(pd.vel[0]);
+  const Dev<S> vy = dev<S>(pd.vel[1]);
+  const Dev<S> vz = dev<S>(pd.vel[2]);
   rho[dst] = rho[src];
   vx[dst] = vx[src];
   vy[dst] = vy[src];

@@ -129,7 +129,7 @@ hipError_t launch_box_state(const PatchDev *cur, const PatchDev *old, const Patc
 // quantities.
 struct CaptureRow {
   int32_t patch, i1, i2, j;
-  double *dst;
+  Dev<double> dst;
   int64_t fstride;
 };
 
@@ -141,8 +141,8 @@ hipError_t launch_capture(const PatchDev *patches, const CaptureRow *rows, int32
 
 // acc[i] += reg[i] over the listed register blocks (prefix over their sizes).
 struct AccItem {
-  double *acc;
-  const double *reg;
+  Dev<double> acc;
+  Dev<const double> reg;
 };
 hipError_t launch_accumulate(const AccItem *items, const int64_t *prefix, int32_t nitems,
                              int64_t total, hipStream_t s);
@@ -156,8 +156,8 @@ struct CorrTarget {
   int64_t cell;
 };
 struct CorrContrib {
-  const double *cap;
-  const double *fine;
+  Dev<const double> cap;
+  Dev<const double> fine;
   int64_t cap_fstride, fine_fstride;
   int32_t fine_row, r, side, axis;
 };

@@ -93,7 +93,7 @@ template <class Prec, bool kCFL, bool kUseHLLC, bool kGrav>
 __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRef<typename Prec::S> &pc, double dt,
                               double lam, double hgdt, int j, bool mine, bool need_face,
                               const CellLoad &in, uint32_t &n_fallback, uint32_t &n_floor,
-                              CflAcc &cfl) {
+                              const CflAcc &cfl) {
   using S = typename Prec::S;
   using T = typename Prec::T;
   const int n = pc.n, g = pc.g;
@@ -245,19 +245,16 @@ __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRe
 #pragma unroll
     for (int k = 0; k < 6; ++k) pc.reg_hi[pc.lab[k] * pc.reg_stride] = dt * F.get(k);
   }
-  double sig = 0.0;
   if (cell_ok && mine) {
+    // (the timestep first: what waits for a later load waits for the stores too)
+    if (kCFL) cfl_take<S>(P, cfl, S(out[0]), S(out[1]), S(out[2]), S(out[3]), out[4], out[5]);
     pc.rho[o] = S(out[0]);
     pc.u[o] = S(out[1]);
     pc.v1[o] = S(out[2]);
     pc.v2[o] = S(out[3]);
     pc.E[o] = out[4];
     pc.e[o] = out[5];
-    if (kCFL)
-      sig = cell_signal<S>(P, cfl.axis, cfl.dx, S(out[0]), S(out[1]), S(out[2]), S(out[3]),
-                           out[4], out[5]);
   }
-  if (kCFL) cfl.smax = sig > cfl.smax ? sig : cfl.smax;  // per lane; reduced at the end
   return F;
 }
 
@@ -267,7 +264,7 @@ __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRe
 template <class Prec, bool kCFL, bool kUseHLLC, bool kGrav>
 __device__ void sweep_rows_lanes(const Params &P, const PatchDev &pd, int axis, int mask,
                                  int first, int step, int nrows, double dt, double a,
-                                 uint32_t &n_fallback, uint32_t &n_floor, CflAcc &cfl) {
+                                 uint32_t &n_fallback, uint32_t &n_floor, const CflAcc &cfl) {
   using S = typename Prec::S;
   const int lane = threadIdx.x & 63;
   const int n = (axis == 0 ? pd.n[0] : (axis == 1 ? pd.n[1] : pd.n[2])) + 2 * pd.ghost;
