@@ -132,7 +132,9 @@ int64_t sweep_pencils(const PatchDev &d, int axis, int tm) {
 // y sweep 526 us with one, 655 with two).
 int32_t choose_run_segments(const PatchDev *d, int32_t npatch, ppm_precision prec, int axis,
                             int tm, int cus) {
-  const double simds = 4.0 * (cus > 0 ? cus : 256);
+  // of thousands of patches a sample of them stands for all
+  const int32_t skip = (npatch + 511) / 512;
+  const double simds = 4.0 * (cus > 0 ? cus : 256) / skip;
   int64_t cells = 0;
   for (int32_t i = 0; i < npatch; ++i)
     cells += sweep_pencils(d[i], axis, 0) * (d[i].n[axis] + 2 * d[i].ghost);
@@ -140,9 +142,10 @@ int32_t choose_run_segments(const PatchDev *d, int32_t npatch, ppm_precision pre
   const int32_t most = axis != 0 && bytes > (int64_t(1) << 27) ? 1 : ppm::kMaxRunSegments;
   int32_t best = 1;
   double best_cost = std::numeric_limits<double>::infinity();
-  for (int32_t segs = 1; segs <= most; ++segs) {
+  for (const int32_t segs : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, ppm::kMaxRunSegments}) {
+    if (segs > most) break;
     double waves = 0.0, work = 0.0;
-    for (int32_t i = 0; i < npatch; ++i) {
+    for (int32_t i = 0; i < npatch; i += skip) {
       const int n = d[i].n[axis] + 2 * d[i].ghost;
       const int64_t np = sweep_pencils(d[i], axis, tm);
       const int64_t rows = ppm::rows_per_wave(n, segs);

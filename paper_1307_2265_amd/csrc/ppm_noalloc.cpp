@@ -29,18 +29,29 @@ namespace {
 constexpr int kMaxPatches = PPM_NOALLOC_MAX_PATCHES;
 constexpr int kMaxLevels = PPM_NOALLOC_MAX_PATCHES;
 constexpr int kMaxDevices = 64;
-constexpr int kSlots = 25;  // 12 marching and 12 lane-parallel sweep maps, then the CFL map
-constexpr int kStride = kMaxPatches + 1;
+// The maps a call can need: of the sweep's twelve (axis, extent) kinds the three
+// of its sweep order, then the CFL map.
+constexpr int kMaps = 4;
 constexpr int kCflCells = 4096;
 
-// Layout of the scratch array.
-constexpr size_t kPatchOff = 0;
-constexpr size_t kChunkOff = kPatchOff + sizeof(PatchDev) * kMaxPatches;
-constexpr size_t kCountOff = (kChunkOff + sizeof(int32_t) * kSlots * kStride + 255) / 256 * 256;
-constexpr size_t kSmaxOff = kCountOff + 2 * sizeof(unsigned long long);
-constexpr size_t kUsedBytes = kSmaxOff + kMaxLevels * sizeof(unsigned long long);
-static_assert(kUsedBytes <= PPM_NOALLOC_SCRATCH_BYTES, "scratch layout exceeds its size");
-static_assert(kChunkOff % 8 == 0 && kCountOff % 8 == 0, "alignment");
+// Layout of the scratch array for a call's patches: event counters, per-level
+// maxima, patch table, maps.  Packed, so that a call uploads only what its own
+// patches take (one patch: 46 words, one launch where the full layout took five).
+struct Layout {
+  size_t count, smax, patch, chunk, bytes;
+};
+constexpr Layout layout(int npatch, int nlevels) {
+  Layout l{};
+  l.count = 0;
+  l.smax = l.count + 2 * sizeof(unsigned long long);
+  l.patch = l.smax + nlevels * sizeof(unsigned long long);
+  l.chunk = l.patch + npatch * sizeof(PatchDev);
+  l.bytes = l.chunk + sizeof(int32_t) * kMaps * (npatch + 1);
+  return l;
+}
+constexpr size_t kMostBytes = layout(kMaxPatches, kMaxLevels).bytes;
+static_assert(kMostBytes <= PPM_NOALLOC_SCRATCH_BYTES, "scratch layout exceeds its size");
+static_assert(sizeof(PatchDev) % 8 == 0, "alignment");
 
 const int kOrders[6][3] = {{0, 1, 2}, {2, 1, 0}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}};
 
@@ -71,69 +82,61 @@ ppm_status scratch_address(unsigned char **out) {
   return PPM_OK;
 }
 
-inline int t1_of(int axis) { return axis == 0 ? 1 : 0; }
-inline int t2_of(int axis) { return axis == 2 ? 1 : 2; }
+inline int tmask_of(int axis, int mask) {
+  const int t1 = axis == 0 ? 1 : 0, t2 = axis == 2 ? 1 : 2;
+  return ((mask >> t1) & 1) | (((mask >> t2) & 1) << 1);
+}
 
-// Launch shapes of the call: as a plan over the same patches with the
-// default tile configuration, per-sweep launches (no persistent launch, no
+// Launch shapes of the call's three sweeps, in its order: as a plan over the
+// same patches with the default tile configuration, per-sweep launches (no
 // grouped maps: each block belongs to one patch).
-struct Shapes {
-  int32_t block, lanes_block, lanes_mask;
-  int32_t lane_segs[12];
-  int32_t nblocks[kSlots];
-  int32_t tail_pencil0[2][12], tail_main[2][12], tail_blocks[2][12];
+struct Shape {
+  int32_t axis, mask;
+  bool lanes;
+  int32_t segs, nblocks;
+  int32_t tail_pencil0, tail_main, tail_blocks;
 };
 
 template <class Prec>
-hipError_t sweep(const Shapes &sh, const PatchDev *patches, const int32_t *chunks, int npatch,
-                 int axis, int mask, const double *dt, const ppm::Params &P,
+hipError_t sweep(const Shape &sh, int32_t block, int32_t lanes_block, const PatchDev *patches,
+                 const int32_t *chunks, int npatch, const double *dt, const ppm::Params &P,
                  unsigned long long *counters, unsigned long long *smax, hipStream_t s) {
-  const int tm = ((mask >> t1_of(axis)) & 1) | (((mask >> t2_of(axis)) & 1) << 1);
-  if ((sh.lanes_mask >> axis) & 1) {  // cells across the lanes
-    const int slot = 12 + axis * 4 + tm;
-    if (sh.nblocks[slot] == 0) return hipSuccess;
-    return ppm::launch_sweep_lanes<Prec>(patches, chunks + slot * kStride, npatch,
-                                         sh.nblocks[slot], sh.lanes_block, axis, mask,
-                                         sh.lane_segs[axis * 4 + tm], dt, P, counters, smax, s);
-  }
-  const int slot = axis * 4 + tm, c = smax ? 1 : 0;
-  const int32_t *cs = chunks + slot * kStride;
-  if (sh.nblocks[slot] == 0) return hipSuccess;
-  if (sh.tail_blocks[c][slot] > 0) {
-    hipError_t e = ppm::launch_sweep<Prec>(patches, cs, npatch, sh.tail_main[c][slot], sh.block,
-                                           axis, mask, dt, P, counters, smax, nullptr, 0, s);
+  if (sh.nblocks == 0) return hipSuccess;
+  if (sh.lanes)
+    return ppm::launch_sweep_lanes<Prec>(patches, chunks, npatch, sh.nblocks, lanes_block, sh.axis,
+                                         sh.mask, sh.segs, dt, P, counters, smax, s);
+  if (sh.tail_blocks > 0) {
+    hipError_t e = ppm::launch_sweep<Prec>(patches, chunks, npatch, sh.tail_main, block, sh.axis,
+                                           sh.mask, dt, P, counters, smax, nullptr, 0, s);
     if (e != hipSuccess) return e;
-    return ppm::launch_sweep_tail<Prec>(patches, cs, sh.tail_blocks[c][slot], sh.lanes_block,
-                                        axis, mask, sh.tail_pencil0[c][slot], dt, P, counters,
-                                        smax, s);
+    return ppm::launch_sweep_tail<Prec>(patches, chunks, sh.tail_blocks, lanes_block, sh.axis,
+                                        sh.mask, sh.tail_pencil0, dt, P, counters, smax, s);
   }
-  return ppm::launch_sweep<Prec>(patches, cs, npatch, sh.nblocks[slot], sh.block, axis, mask, dt,
+  return ppm::launch_sweep<Prec>(patches, chunks, npatch, sh.nblocks, block, sh.axis, sh.mask, dt,
                                  P, counters, smax, nullptr, 0, s);
 }
 
 template <class Prec>
-hipError_t run(const Shapes &sh, const PatchDev *host, const int32_t *bc, unsigned char *base,
-               int npatch,
-               int nlevels, const ppm::Params &P, double *dt, int sweep_order, uint32_t parts,
-               int32_t cfl_blocks, hipStream_t s) {
-  const PatchDev *patches = reinterpret_cast<const PatchDev *>(base + kPatchOff);
-  const int32_t *chunks = reinterpret_cast<const int32_t *>(base + kChunkOff);
-  unsigned long long *counters = reinterpret_cast<unsigned long long *>(base + kCountOff);
-  unsigned long long *smax = reinterpret_cast<unsigned long long *>(base + kSmaxOff);
+hipError_t run(const Shape (&shapes)[3], int32_t block, int32_t lanes_block, const PatchDev *host,
+               const int32_t *bc, unsigned char *base, int npatch, int nlevels,
+               const ppm::Params &P, double *dt, uint32_t parts, int32_t cfl_blocks,
+               hipStream_t s) {
+  const Layout l = layout(npatch, nlevels);
+  const PatchDev *patches = reinterpret_cast<const PatchDev *>(base + l.patch);
+  const int32_t *chunks = reinterpret_cast<const int32_t *>(base + l.chunk);
+  unsigned long long *counters = reinterpret_cast<unsigned long long *>(base + l.count);
+  unsigned long long *smax = reinterpret_cast<unsigned long long *>(base + l.smax);
+  const int stride = npatch + 1;
   hipError_t e = hipSuccess;
   if (parts & PPM_NOALLOC_FILL)
     for (int i = 0; i < npatch && e == hipSuccess; ++i)
       if (bc[i] == PPM_BC_PERIODIC) e = ppm::launch_fill<Prec>(host[i], s);
   if (e == hipSuccess && (parts & PPM_NOALLOC_CFL))
-    e = ppm::launch_cfl<Prec>(patches, chunks + 24 * kStride, npatch, cfl_blocks, kCflCells,
+    e = ppm::launch_cfl<Prec>(patches, chunks + 3 * stride, npatch, cfl_blocks, kCflCells,
                               nlevels, P, smax, dt, s);
-  int mask = 0;
-  for (int k = 0; k < 3 && e == hipSuccess; ++k) {
-    const int axis = kOrders[sweep_order][k];
-    e = sweep<Prec>(sh, patches, chunks, npatch, axis, mask, dt, P, counters,
-                    k == 2 ? smax : nullptr, s);
-    mask |= 1 << axis;
-  }
+  for (int k = 0; k < 3 && e == hipSuccess; ++k)
+    e = sweep<Prec>(shapes[k], block, lanes_block, patches, chunks + k * stride, npatch, dt, P,
+                    counters, k == 2 ? smax : nullptr, s);
   if (e == hipSuccess) e = ppm::launch_cfl_finalize(nlevels, P.cfl, nullptr, smax, dt, s);
   return e;
 }
@@ -185,91 +188,90 @@ extern "C" ppm_status ppm_step_cfl_noalloc(const ppm_patch *patches, int32_t npa
       if (patches[i].bc != PPM_BC_PERIODIC)
         return fail(PPM_EINVAL, "patch %d: PPM_NOALLOC_FILL needs PPM_BC_PERIODIC patches", i);
 
-  // launch maps (prefix arrays of work chunks per sweep slot, then the CFL map)
-  Shapes sh;
-  std::memset(&sh, 0, sizeof sh);
-  sh.block = npatch == 1 ? 256 : 64;
-  sh.lanes_block = npatch == 1 ? 256 : 64;
+  // launch maps (prefix arrays of work chunks of the three sweeps, then the
+  // CFL map) and shapes; one patch marched: whole rounds of one marching block
+  // per compute unit, the few pencils left over to the lane-parallel tail launch
+  // (as a one-patch plan does)
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     cus = 0;
-  sh.lanes_mask = ppm_detail::default_lanes(host, npatch, cus);
-  int32_t chunks[kSlots * kStride];
+  const int32_t block = npatch == 1 ? 256 : 64, lanes_block = block;
+  const int32_t lanes_mask = ppm_detail::default_lanes(host, npatch, cus);
+  const int stride = npatch + 1;
+  Shape shapes[3];
+  std::memset(shapes, 0, sizeof shapes);
+  int32_t chunks[kMaps * (kMaxPatches + 1)];
   std::memset(chunks, 0, sizeof chunks);
-  for (int kind = 0; kind < 2; ++kind)
-    for (int axis = 0; axis < 3; ++axis)
-      for (int tm = 0; tm < 4; ++tm) {
-        const int slot = kind * 12 + axis * 4 + tm;
-        int64_t acc = 0;
-        const int32_t segs = kind == 1 && ((sh.lanes_mask >> axis) & 1)
-            ? ppm_detail::choose_run_segments(host, npatch, prec, axis, tm, cus) : 1;
-        if (kind == 1) sh.lane_segs[axis * 4 + tm] = segs;
-        for (int i = 0; i < npatch; ++i) {
-          const PatchDev &d = host[i];
-          int64_t items = ppm_detail::sweep_pencils(d, axis, tm), per_block = sh.block;
-          if (kind == 1) {
-            const int64_t rpw = ppm::rows_per_wave(d.n[axis] + 2 * d.ghost, segs);
-            items = (items + rpw - 1) / rpw;
-            per_block = sh.lanes_block / 64;
-          }
-          chunks[slot * kStride + i] = int32_t(acc);
-          acc += (items + per_block - 1) / per_block;
-          if (acc > INT32_MAX / 2) return fail(PPM_EINVAL, "too many pencils for one launch");
-        }
-        chunks[slot * kStride + npatch] = int32_t(acc);
-        sh.nblocks[slot] = int32_t(acc);
+  int mask = 0;
+  for (int k = 0; k < 3; ++k) {
+    Shape &sh = shapes[k];
+    const int axis = kOrders[sweep_order][k], tm = tmask_of(axis, mask);
+    sh.axis = axis;
+    sh.mask = mask;
+    sh.lanes = (lanes_mask >> axis) & 1;
+    if (sh.lanes) sh.segs = ppm_detail::choose_run_segments(host, npatch, prec, axis, tm, cus);
+    int64_t acc = 0;
+    for (int i = 0; i < npatch; ++i) {
+      const PatchDev &d = host[i];
+      int64_t items = ppm_detail::sweep_pencils(d, axis, tm), per_block = block;
+      if (sh.lanes) {
+        const int64_t rpw = ppm::rows_per_wave(d.n[axis] + 2 * d.ghost, sh.segs);
+        items = (items + rpw - 1) / rpw;
+        per_block = lanes_block / 64;
       }
+      chunks[k * stride + i] = int32_t(acc);
+      acc += (items + per_block - 1) / per_block;
+      if (acc > INT32_MAX / 2) return fail(PPM_EINVAL, "too many pencils for one launch");
+    }
+    chunks[k * stride + npatch] = int32_t(acc);
+    sh.nblocks = int32_t(acc);
+    if (npatch == 1 && cus > 0 && !sh.lanes) {
+      const int64_t cap = int64_t(cus) * block;
+      const int64_t np = ppm_detail::sweep_pencils(host[0], axis, tm), rest = np % cap;
+      if (np >= cap && rest != 0 && rest * 8 <= cap) {
+        sh.tail_pencil0 = int32_t(np - rest);
+        sh.tail_main = int32_t((np - rest) / block);
+        sh.tail_blocks = int32_t((rest + lanes_block / 64 - 1) / (lanes_block / 64));
+      }
+    }
+    mask |= 1 << axis;
+  }
   int32_t cfl_blocks = 0;
   {
     int64_t acc = 0;
     for (int i = 0; i < npatch; ++i) {
       const PatchDev &d = host[i];
-      chunks[24 * kStride + i] = int32_t(acc);
+      chunks[3 * stride + i] = int32_t(acc);
       acc += (int64_t(d.n[0]) * d.n[1] * d.n[2] + kCflCells - 1) / kCflCells;
       if (acc > INT32_MAX / 2) return fail(PPM_EINVAL, "too many cells for one CFL launch");
     }
-    chunks[24 * kStride + npatch] = int32_t(acc);
+    chunks[3 * stride + npatch] = int32_t(acc);
     cfl_blocks = int32_t(acc);
   }
-  // one patch: whole rounds of one marching block per compute unit, the few
-  // pencils left over to the lane-parallel tail launch (as a one-patch plan
-  // does)
-  if (npatch == 1 && cus > 0)
-    for (int c = 0; c < 2; ++c) {
-      const int64_t cap = int64_t(cus) * sh.block;
-      if (cap <= 0) continue;
-      for (int slot = 0; slot < 12; ++slot) {
-        const int axis = slot / 4, tm = slot % 4;
-        const int64_t np = ppm_detail::sweep_pencils(host[0], axis, tm), rest = np % cap;
-        if (np < cap || rest == 0 || rest * 8 > cap) continue;
-        sh.tail_pencil0[c][slot] = int32_t(np - rest);
-        sh.tail_main[c][slot] = int32_t((np - rest) / sh.block);
-        sh.tail_blocks[c][slot] = int32_t((rest + sh.lanes_block / 64 - 1) / (sh.lanes_block / 64));
-      }
-    }
 
   unsigned char *base = nullptr;
   if ((st = scratch_address(&base)) != PPM_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  // the table, the maps, and zeroed counters and maxima (the previous call's
-  // contents are all replaced)
-  uint32_t words[kUsedBytes / 4];
-  std::memset(words, 0, sizeof words);
-  std::memcpy(reinterpret_cast<unsigned char *>(words) + kPatchOff, host, sizeof host);
-  std::memcpy(reinterpret_cast<unsigned char *>(words) + kChunkOff, chunks, sizeof chunks);
+  // zeroed counters and maxima, the table and the maps (whatever a previous call
+  // left there is replaced as far as this call reads)
+  const Layout l = layout(npatch, nlevels);
+  uint32_t words[kMostBytes / 4];
+  std::memset(words, 0, l.patch);
+  unsigned char *bytes = reinterpret_cast<unsigned char *>(words);
+  std::memcpy(bytes + l.patch, host, sizeof(PatchDev) * size_t(npatch));
+  std::memcpy(bytes + l.chunk, chunks, sizeof(int32_t) * size_t(kMaps) * size_t(stride));
   hipError_t e = ppm::launch_write_words(reinterpret_cast<uint32_t *>(base), words,
-                                         int64_t(kUsedBytes / 4), s);
+                                         int64_t(l.bytes / 4), s);
   if (e != hipSuccess) return hip_fail(e, "scratch upload");
-  e = prec == PPM_FP64
-          ? run<ppm::PrecF64>(sh, host, bc, base, npatch, nlevels, P, dt_dev, sweep_order,
-                              parts, cfl_blocks, s)
-          : run<ppm::PrecMixed>(sh, host, bc, base, npatch, nlevels, P, dt_dev, sweep_order,
-                                parts, cfl_blocks, s);
+  e = prec == PPM_FP64 ? run<ppm::PrecF64>(shapes, block, lanes_block, host, bc, base, npatch,
+                                           nlevels, P, dt_dev, parts, cfl_blocks, s)
+                       : run<ppm::PrecMixed>(shapes, block, lanes_block, host, bc, base, npatch,
+                                             nlevels, P, dt_dev, parts, cfl_blocks, s);
   if (e != hipSuccess) return hip_fail(e, "ppm_step_cfl_noalloc launch");
   if (events) {
     unsigned long long h[2] = {0, 0};
-    e = hipMemcpyAsync(h, base + kCountOff, sizeof h, hipMemcpyDeviceToHost, s);
+    e = hipMemcpyAsync(h, base + l.count, sizeof h, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "event counter read");
     events[0] = int64_t(h[0]);
