@@ -858,8 +858,7 @@ capture_kernel(const PatchDev *__restrict__ patches, const CaptureRow *__restric
   const bool used = slot < kCapPerWave && row0 + slot < nrows;
   const CaptureRow cr = rows[used ? row0 + slot : row0];
   const PatchDev pd = patches[cr.patch];
-  PencilRef<S> pc = make_pencil<S>(pd, axis, cr.i1, cr.i2);
-  pc.reg_lo = pc.reg_hi = nullptr;
+  const PencilRef<S> pc = make_pencil<S>(pd, axis, cr.i1, cr.i2);
   const double dt = dt_dev[pd.level];
   const double a = expansion_a(P, pd.level);
   const double lam = dt / (a * pc.dx);
@@ -879,8 +878,9 @@ capture_kernel(const PatchDev *__restrict__ patches, const CaptureRow *__restric
   // the face's final flux reads the provisional fluxes of faces j-1/2 ..
   // j+3/2 (the fallback tests of cells j and j+1)
   const bool need_face = pos >= 3 && pos <= 5;
-  const auto F = sweep_segment<Prec, false, kUseHLLC, kGrav>(P, pc, dt, lam, hgdt, j, false,
-                                                             need_face, cur, nfb, nfl, cfl);
+  const auto F = sweep_segment<Prec, false, kUseHLLC, kGrav>(P, nullptr, axis, pc, pc.base, 0, 0,
+                                                             dt, lam, hgdt, j, false, need_face,
+                                                             cur, nfb, nfl, cfl);
   if (used && pos == 4) {
 #pragma unroll
     for (int k = 0; k < 6; ++k) cr.dst[pc.lab[k] * cr.fstride] = dt * F.get(k);

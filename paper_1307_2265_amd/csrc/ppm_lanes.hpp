@@ -80,8 +80,10 @@ struct CellLoad {
   double r, u, v1, v2, E, e;
 };
 
-// One segment: lane holds cell j of pencil pc (j = -1 for a placeholder
-// lane beyond the stream, which no valid result uses).  `in` is this lane's
+// One segment: lane holds cell j of pencil (i1, i2) (j = -1 for a placeholder
+// lane beyond the stream, which no valid result uses), whose cell 0 lies at
+// offset base; pc gives the fields (not its own offset), pd the patch whose
+// boundary registers are written (nullable).  `in` is this lane's
 // input cell; the lane writes its cell (and counts its events) if `mine`,
 // and solves the Riemann problem of its face j+1/2 only if `need_face` (the
 // face's provisional flux can reach a written cell or the face the caller
@@ -90,10 +92,11 @@ struct CellLoad {
 // factor (the same for every pencil of the patch).  Returns the final flux
 // (after the fallback) of face j+1/2.
 template <class Prec, bool kCFL, bool kUseHLLC, bool kGrav>
-__device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRef<typename Prec::S> &pc, double dt,
-                              double lam, double hgdt, int j, bool mine, bool need_face,
-                              const CellLoad &in, uint32_t &n_fallback, uint32_t &n_floor,
-                              const CflAcc &cfl) {
+__device__ __forceinline__ FluxT<typename Prec::T> sweep_segment(
+    const Params &P, const PatchDev *pd_reg, int axis, const PencilRef<typename Prec::S> &pc,
+    int64_t base, int i1, int i2, double dt, double lam, double hgdt, int j, bool mine,
+    bool need_face, const CellLoad &in, uint32_t &n_fallback, uint32_t &n_floor,
+    const CflAcc &cfl) {
   using S = typename Prec::S;
   using T = typename Prec::T;
   const int n = pc.n, g = pc.g;
@@ -106,7 +109,7 @@ __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRe
 
   // ---- equation of state
   const bool has = j >= 0 && j < n;
-  const int64_t o = pc.base + int64_t(has ? j : 0) * pc.stride;
+  const int64_t o = base + int64_t(has ? j : 0) * pc.stride;
   const double r = in.r, u = in.u, v1 = in.v1, v2 = in.v2, E = in.E, e = in.e;
   const double pd = eos_pressure(P, r, u, v1, v2, E, e);
   T q[5] = {T(r), T(u), T(v1), T(v2), T(pd)};
@@ -237,13 +240,16 @@ __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRe
   }
 
   // ---- boundary flux registers and write-back
-  if (pc.reg_lo && j == a0 - 1 && mine_next) {
+  if (pd_reg && pd_reg->flux_reg) {
+    const bool low = j == a0 - 1 && mine_next, high = j == a1 && mine;
+    if (low || high) {
+      int64_t stride;
+      const Dev<double> reg = register_slot(*pd_reg, axis, i1, i2, high, stride);
+      if (reg) {
 #pragma unroll
-    for (int k = 0; k < 6; ++k) pc.reg_lo[pc.lab[k] * pc.reg_stride] = dt * F.get(k);
-  }
-  if (pc.reg_hi && j == a1 && mine) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) pc.reg_hi[pc.lab[k] * pc.reg_stride] = dt * F.get(k);
+        for (int k = 0; k < 6; ++k) reg[pc.lab[k] * stride] = dt * F.get(k);
+      }
+    }
   }
   if (cell_ok && mine) {
     // (the timestep first: what waits for a later load waits for the stores too)
@@ -259,28 +265,45 @@ __device__ FluxT<typename Prec::T> sweep_segment(const Params &P, const PencilRe
 }
 
 // One wave streams the pencils first, first + step, ... (nrows of them) of a
-// sweep's pencil set, concatenated, segment by segment.
+// sweep's pencil set, concatenated, segment by segment.  A lane's place (row of
+// the run, cell j, transverse indices i1, i2, offset of the pencil's cell 0)
+// moves from segment to segment by additions and two conditional wraps, the
+// divisions behind the steps being done once: 54 cells on is `drow` pencils
+// and `dj` cells on, and one pencil more where that passes the pencil's end.
+// (Found anew for each segment it took 85 instructions of about 1630, 1140 in
+// the mixed precision.)
 // a: the patch level's expansion factor.
 template <class Prec, bool kCFL, bool kUseHLLC, bool kGrav>
-__device__ void sweep_rows_lanes(const Params &P, const PatchDev &pd, int axis, int mask,
-                                 int first, int step, int nrows, double dt, double a,
-                                 uint32_t &n_fallback, uint32_t &n_floor, const CflAcc &cfl) {
+__device__ __forceinline__ void sweep_rows_lanes(const Params &P, const PatchDev &pd, int axis,
+                                                 int mask, int first, int step, int nrows,
+                                                 double dt, double a, uint32_t &n_fallback,
+                                                 uint32_t &n_floor, const CflAcc &cfl) {
   using S = typename Prec::S;
   const int lane = threadIdx.x & 63;
-  const int n = (axis == 0 ? pd.n[0] : (axis == 1 ? pd.n[1] : pd.n[2])) + 2 * pd.ghost;
-  const int L = nrows * n;
-  const int nseg = run_segments(L);
-  const double lam = dt / (a * pick3(axis, pd.dx[0], pd.dx[1], pd.dx[2]));
+  const PencilRef<S> pc = make_pencil<S>(pd, axis, 0, 0);
+  const int n = pc.n;
+  const int nseg = run_segments(nrows * n);
+  const double lam = dt / (a * pc.dx);
   const double hgdt = 0.5 * dt / a;
+  // the transverse range of the sweep's pencils, and the offsets of a step along it
+  const int t1 = axis == 0 ? 1 : 0;
+  const int N1 = pick3(t1, pd.n[0], pd.n[1], pd.n[2]);
+  const bool r1 = (mask >> t1) & 1;
+  const int lo1 = r1 ? pd.ghost : 0, w1 = r1 ? N1 : N1 + 2 * pd.ghost;
+  const int64_t nfx = int64_t(pd.n[0]) + 2 * pd.ghost, nfy = int64_t(pd.n[1]) + 2 * pd.ghost;
+  const int64_t s1 = axis == 0 ? nfx : 1, s2 = axis == 2 ? nfx : nfx * nfy;
+  const int drow = kLaneOut / n, dj = kLaneOut - drow * n;
+  // drow pencils of the run on, and one more
+  const int d1[2] = {drow * step % w1, (drow + 1) * step % w1};
+  const int d2[2] = {drow * step / w1, (drow + 1) * step / w1};
+  int row = lane / n, j = lane - row * n;
+  const int t2 = axis == 2 ? 1 : 2;
+  int i1 = lo1 + (first + row * step) % w1;
+  int i2 = (((mask >> t2) & 1) ? pd.ghost : 0) + (first + row * step) / w1;
+  int64_t base = i1 * s1 + i2 * s2;
   CellLoad cur = {1.0, 0.0, 0.0, 0.0, 1.0, 1.0};
   for (int s = 0; s < nseg; ++s) {
-    const int t = s * kLaneOut + lane;  // stream position of this lane
-    const bool in = t < L;
-    const int row = in ? t / n : 0;
-    const int j = in ? t - row * n : -1;
-    int i1 = pd.ghost, i2 = pd.ghost;
-    pencil_index(pd, axis, mask, first + row * step, i1, i2);
-    const PencilRef<S> pc = make_pencil<S>(pd, axis, i1, i2);
+    const bool in = row < nrows;
     // the first 2*halo lanes overlap the previous segment's last lanes
     CellLoad prev;
     prev.r = __shfl(cur.r, lane + kLaneOut, 64);
@@ -292,7 +315,7 @@ __device__ void sweep_rows_lanes(const Params &P, const PatchDev &pd, int axis, 
     if (s > 0 && lane < 2 * kLaneHalo) {
       cur = prev;
     } else if (in) {
-      const int64_t o = pc.base + int64_t(j) * pc.stride;
+      const int64_t o = base + int64_t(j) * pc.stride;
       cur.r = double(pc.rho[o]); cur.u = double(pc.u[o]);
       cur.v1 = double(pc.v1[o]); cur.v2 = double(pc.v2[o]);
       cur.E = pc.E[o]; cur.e = pc.e[o];
@@ -307,8 +330,19 @@ __device__ void sweep_rows_lanes(const Params &P, const PatchDev &pd, int axis, 
     // the written cells' faces, and the provisional fluxes of the faces one
     // further out that the fallback tests of the end cells read
     const bool need_face = lane >= lo - 2 && lane <= hi;
-    sweep_segment<Prec, kCFL, kUseHLLC, kGrav>(P, pc, dt, lam, hgdt, j, mine, need_face, cur,
-                                               n_fallback, n_floor, cfl);
+    sweep_segment<Prec, kCFL, kUseHLLC, kGrav>(P, &pd, axis, pc, base, i1, i2, dt, lam, hgdt,
+                                               in ? j : -1, mine, need_face, cur, n_fallback,
+                                               n_floor, cfl);
+    j += dj;
+    const bool over = j >= n;
+    j -= over ? n : 0;
+    row += drow + (over ? 1 : 0);
+    const int e1 = over ? d1[1] : d1[0], e2 = over ? d2[1] : d2[0];
+    i1 += e1;
+    const bool wrap = i1 >= lo1 + w1;
+    i1 -= wrap ? w1 : 0;
+    i2 += e2 + (wrap ? 1 : 0);
+    base = i1 * s1 + i2 * s2;
   }
 }
 

@@ -117,6 +117,21 @@ __device__ __forceinline__ int64_t reg_face_offset(int64_t nx, int64_t ny, int64
   return 6 * (before + (hi ? pick3<int64_t>(axis, ax, ay, az) : 0));
 }
 
+// Where the boundary flux of the pencil (i1, i2) goes in the patch's flux
+// register (face 2 axis + hi), and the stride between the six register fields
+// there; null for a pencil outside the transverse active range.
+__device__ __forceinline__ Dev<double> register_slot(const PatchDev &pd, int axis, int i1, int i2,
+                                                     int hi, int64_t &stride) {
+  const int t1 = axis == 0 ? 1 : 0, t2 = axis == 2 ? 1 : 2;
+  const int g = pd.ghost;
+  const int Nt1 = pick3(t1, pd.n[0], pd.n[1], pd.n[2]);
+  const int Nt2 = pick3(t2, pd.n[0], pd.n[1], pd.n[2]);
+  stride = int64_t(Nt1) * Nt2;
+  if (!pd.flux_reg || i1 < g || i1 >= g + Nt1 || i2 < g || i2 >= g + Nt2) return nullptr;
+  return pd.flux_reg + reg_face_offset(pd.n[0], pd.n[1], pd.n[2], axis, hi) +
+         int64_t(i2 - g) * Nt1 + (i1 - g);
+}
+
 // The pencil (i1, i2) of a sweep along `axis` of one patch.
 template <class S>
 __device__ __forceinline__ PencilRef<S> make_pencil(const PatchDev &pd, int axis, int i1, int i2) {
@@ -124,7 +139,7 @@ __device__ __forceinline__ PencilRef<S> make_pencil(const PatchDev &pd, int axis
   const int g = pd.ghost;
   const int N0 = pd.n[0], N1 = pd.n[1], N2 = pd.n[2];
   const int nf0 = N0 + 2 * g, nf1 = N1 + 2 * g;
-  const int Na = pick3(axis, N0, N1, N2), Nt1 = pick3(t1, N0, N1, N2), Nt2 = pick3(t2, N0, N1, N2);
+  const int Na = pick3(axis, N0, N1, N2);
   const int64_t sx = 1, sy = nf0, sz = int64_t(nf0) * nf1;
   PencilRef<S> pc;
   pc.rho = dev<S>(pd.rho);
@@ -138,17 +153,11 @@ __device__ __forceinline__ PencilRef<S> make_pencil(const PatchDev &pd, int axis
   pc.n = Na + 2 * g;
   pc.g = g;
   pc.dx = pick3(axis, pd.dx[0], pd.dx[1], pd.dx[2]);
-  pc.reg_lo = pc.reg_hi = nullptr;
-  pc.reg_stride = 0;
   pc.lab[0] = 0; pc.lab[1] = 1 + axis; pc.lab[2] = 1 + t1; pc.lab[3] = 1 + t2;
   pc.lab[4] = 4; pc.lab[5] = 5;
   pc.acc = dev<const S>(pick3(axis, pd.acc[0], pd.acc[1], pd.acc[2]));
-  if (pd.flux_reg && i1 >= g && i1 < g + Nt1 && i2 >= g && i2 < g + Nt2) {
-    const int64_t ro = int64_t(i2 - g) * Nt1 + (i1 - g);
-    pc.reg_lo = pd.flux_reg + reg_face_offset(N0, N1, N2, axis, 0) + ro;
-    pc.reg_hi = pd.flux_reg + reg_face_offset(N0, N1, N2, axis, 1) + ro;
-    pc.reg_stride = int64_t(Nt1) * Nt2;
-  }
+  pc.reg_lo = register_slot(pd, axis, i1, i2, 0, pc.reg_stride);
+  pc.reg_hi = register_slot(pd, axis, i1, i2, 1, pc.reg_stride);
   return pc;
 }
 
