@@ -8,13 +8,13 @@ writes each expression in.  Packed FP32 instructions are disabled
 ppm_kernels.hip is compiled four times (PPM_KERNEL_PASS 1 to 4), so that
 each group of sweep kernels takes the LLVM machine scheduler that runs it
 fastest on gfx950 (measured, alternating runs on one box): iterative-ilp for
-the double-precision marching sweeps (and every non-sweep kernel) and for
-the mixed-precision lane-parallel ones, max-ilp for the mixed-precision
-marching sweeps and for the double-precision lane-parallel ones (under
-iterative-ilp their last-sweep build spills four times as much in its
-loop).  Against the default scheduler: 512^3 grid about -1 % (FP64) and
--2.4 % (mixed) per step, 4096-patch batch -1 % and -2 %.  Scheduling
-reorders instructions only, so results are unchanged bit for bit.
+the mixed-precision lane-parallel sweeps (batch of 4096 patches, last x sweep
+1515 -> 1476 us against max-ilp, 1610 with the default scheduler), max-ilp
+for the others.  For the double-precision marching sweeps it replaces
+iterative-ilp: 300^3 y sweep with gravity 2137 -> 1806 us, 300^3 last sweep
+with HLLC 1740 -> 1640, batch last z sweep 1770 -> 1690, 256^3 last sweep
+1126 -> 1100, the rest within 1 %.  Scheduling reorders instructions only,
+so results are unchanged bit for bit.
 """
 from __future__ import annotations
 
@@ -29,7 +29,7 @@ LIB = os.path.join(HERE, "libppm.so")
 # (source, object, extra flags)
 UNITS = [
     ("ppm_kernels.hip", "ppm_kernels_fp64.o",
-     ["-DPPM_KERNEL_PASS=1", "-mllvm", "--amdgpu-sched-strategy=iterative-ilp"]),
+     ["-DPPM_KERNEL_PASS=1", "-mllvm", "--amdgpu-sched-strategy=max-ilp"]),
     ("ppm_kernels.hip", "ppm_kernels_mixed.o",
      ["-DPPM_KERNEL_PASS=2", "-mllvm", "--amdgpu-sched-strategy=max-ilp"]),
     ("ppm_kernels.hip", "ppm_kernels_fp64_lanes.o",
