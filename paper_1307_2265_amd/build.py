@@ -7,14 +7,13 @@ writes each expression in.  Packed FP32 instructions are disabled
 
 ppm_kernels.hip is compiled four times (PPM_KERNEL_PASS 1 to 4), so that
 each group of sweep kernels takes the LLVM machine scheduler that runs it
-fastest on gfx950 (measured, alternating runs on one box): iterative-ilp for
-the mixed-precision lane-parallel sweeps (batch of 4096 patches, last x sweep
-1515 -> 1476 us against max-ilp, 1610 with the default scheduler), max-ilp
-for the others.  For the double-precision marching sweeps it replaces
-iterative-ilp: 300^3 y sweep with gravity 2137 -> 1806 us, 300^3 last sweep
-with HLLC 1740 -> 1640, batch last z sweep 1770 -> 1690, 256^3 last sweep
-1126 -> 1100, the rest within 1 %.  Scheduling reorders instructions only,
-so results are unchanged bit for bit.
+fastest on gfx950 (measured, alternating runs on one box): the default one for
+the double-precision marching sweeps (256^3 last sweep 950 us; max-ilp 975,
+iterative-ilp 1130), max-ilp for the mixed-precision marching sweeps (512^3
+4.74 ms, default 4.79) and the double-precision lane-parallel ones, and
+iterative-ilp for the mixed-precision lane-parallel ones (batch of 4096
+patches, first x sweep 2.10 ms; max-ilp 2.16, default 2.20).  Scheduling
+reorders instructions only, so results are unchanged bit for bit.
 """
 from __future__ import annotations
 
@@ -28,8 +27,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libppm.so")
 # (source, object, extra flags)
 UNITS = [
-    ("ppm_kernels.hip", "ppm_kernels_fp64.o",
-     ["-DPPM_KERNEL_PASS=1", "-mllvm", "--amdgpu-sched-strategy=max-ilp"]),
+    ("ppm_kernels.hip", "ppm_kernels_fp64.o", ["-DPPM_KERNEL_PASS=1"]),
     ("ppm_kernels.hip", "ppm_kernels_mixed.o",
      ["-DPPM_KERNEL_PASS=2", "-mllvm", "--amdgpu-sched-strategy=max-ilp"]),
     ("ppm_kernels.hip", "ppm_kernels_fp64_lanes.o",

@@ -104,6 +104,9 @@ ppm::Params device_params(ppm_precision prec, const ppm_params *p) {
   static_assert(offsetof(ppm::Params, expand) == sizeof(ppm_params), "params layout");
   P.expand = nullptr;
   P.shock_k0 = std::sqrt((p->gamma - 1.0) / (2.0 * p->gamma));
+  P.gm1 = p->gamma - 1.0;
+  P.g1 = (p->gamma + 1.0) / (2.0 * p->gamma);
+  P.steep_gk = p->gamma * ppm::kSteepK0;
   if (prec == PPM_MIXED) {  // floors a float density and pressure can hold exactly
     P.rho_floor = float_at_or_above(p->rho_floor);
     P.p_floor = float_at_or_above(p->p_floor);

@@ -153,7 +153,7 @@ __device__ __forceinline__ FluxT<typename Prec::T> sweep_segment(
   if (steepen) {
     const T d2m = from_left(d2), d2p = from_right(d2);
     const T dmm = from_left(dm[0]), dmp = from_right(dm[0]);
-    T eta = steepen_eta<T>(gam, qm[0], qp[0], qm[4], qp[4], d2m, d2p);
+    T eta = steepen_eta<T>(T(P.steep_gk), qm[0], qp[0], qm[4], qp[4], d2m, d2p);
     if (eta != T(0)) {
       l[0] = mad<T>(l[0], T(1) - eta, xfma(T(0.25), dmm, qm[0]) * eta);
       rr[0] = mad<T>(rr[0], T(1) - eta, xfma(T(-0.25), dmp, qp[0]) * eta);

@@ -48,6 +48,10 @@ struct Params {
   // sqrt((gamma-1)/(2 gamma)): a shock wave's Lagrangian speed over the sound
   // one, W_s / C_s, as the star pressure falls to zero
   double shock_k0;
+  // gamma - 1, (gamma + 1) / (2 gamma) and gamma times the steepening's K0:
+  // formed on the host, they reach the sweeps in scalar registers (formed in
+  // the kernels they hold six vector registers over the whole march)
+  double gm1, g1, steep_gk;
 };
 
 // Expansion factor of a level (1 without expansion factors).
@@ -76,6 +80,15 @@ __device__ __forceinline__ float xfma(float a, float b, float c) {
   return __builtin_fmaf(a, b, c);
 }
 
+// x, of which the compiler knows nothing: what is formed from it on a rare
+// branch of a loop stays there (hoisted, it would hold registers throughout).
+template <class T> __device__ __forceinline__ T opaque(T x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+v"(x));
+#endif
+  return x;
+}
+
 // Correctly rounded double quotient and square root for operands of
 // ordinary magnitude.  Both refine the hardware reciprocal (square root) by
 // fused multiply-adds and finish with one exact-remainder correction, which
@@ -83,7 +96,14 @@ __device__ __forceinline__ float xfma(float a, float b, float c) {
 // root likewise).  The reciprocal is refined by one cubic step, y (1 + e +
 // e^2) with e = 1 - b y: the hardware estimate carries about 24 correct bits,
 // so e^3 lies near 2^-70 and three fused operations do what two quadratic
-// steps take four for.  They omit the operand scaling and
+// steps take four for.  (One quadratic step, 2^-48, is too little here: of 8e9
+// random operands none came out wrong, but 1 / (1 - k ulp) lies k^2 2^-106 above
+// the middle between two doubles, and a quadratic step errs downwards.)  The
+// root takes one quadratic step of the root and of its halved inverse, both
+// from below, and the correction: roots of 1 + k ulp lie as close below such a
+// middle, the side it errs to, and no operand within 2^20 ulps of any of twenty
+// centres, nor of the random ones, gave another result than sqrt.
+// They omit the operand scaling and
 // special-value fix-ups that a general IEEE division or square root needs for
 // operands within 2^768 of the overflow or underflow threshold, zeros,
 // infinities and NaNs.  They serve only where the operands are bounded: the
@@ -112,17 +132,30 @@ __device__ __forceinline__ double drcp(double b) {
   const double y = rcp_cubic(b);
   return fma(fma(-b, y, 1.0), y, y);
 }
-__device__ __forceinline__ double dsqrt(double x) {
+// 1 / b from y, the reciprocal times 1 + 2^-44 to a few 2^-47 (the halved
+// inverse roots that make up b, times kInvBias): two quadratic steps, the second
+// by y again, whose excess lifts the reciprocals that end just above a middle
+// (see above) off the tie.  No hardware reciprocal: its issue takes four times
+// that of another double operation.
+constexpr double kInvBias = 1.0 + 0x1p-44;
+__device__ __forceinline__ double drcp_from(double b, double y) {
+  const double z = fma(fma(-b, y, 1.0), y, y);
+  return fma(fma(-b, z, 1.0), y, z);
+}
+// The root, and h = 1 / (2 sqrt(x)) to about 2^-47 (never above it by more than
+// its rounding).
+__device__ __forceinline__ double dsqrt(double x, double &h) {
   const double y = __builtin_amdgcn_rsq(x);
-  double s = x * y;   // sqrt(x)
-  double h = y * 0.5; // 1 / (2 sqrt(x))
+  double s = x * y;
+  h = y * 0.5;
   const double e = fma(-h, s, 0.5);
   s = fma(s, e, s);
   h = fma(h, e, h);
-  double d = fma(-s, s, x);
-  s = fma(d, h, s);
-  d = fma(-s, s, x);
-  return fma(d, h, s);
+  return fma(fma(-s, s, x), h, s);
+}
+__device__ __forceinline__ double dsqrt(double x) {
+  double h;
+  return dsqrt(x, h);
 }
 
 // Quotient, reciprocal and square root of the reconstruction and tracing
@@ -140,16 +173,19 @@ template <> __device__ __forceinline__ float rdiv<float>(float a, float b) {
 // only the scaling for extreme exponents: the reciprocal needs none for any
 // normal operand, and the root's operand (a product of two edge values, each
 // zero or at least an ulp of the 1e-100 floors) lies far above the 2^-900
-// below which its remainders would turn subnormal.  8 instructions instead of
-// 11, and 13 instead of 19.  In the float stages of the mixed precision the
-// hardware reciprocal.
+// below which its remainders would turn subnormal.  In the float stages of the
+// mixed precision the hardware reciprocal.
 __device__ __forceinline__ double xrcp(double b) {
   return __builtin_amdgcn_div_fixup(drcp(b), b, 1.0);
 }
 __device__ __forceinline__ float xrcp(float b) { return __builtin_amdgcn_rcpf(b); }
-__device__ __forceinline__ double xsqrt(double x) {
-  const double s = dsqrt(x);
-  return x == 0.0 ? x : s;
+// The root and its reciprocal, which starts from the h of the root.
+__device__ __forceinline__ double xsqrt(double x, double &inv) {
+  double h;
+  const double s = dsqrt(x, h);
+  const double root = x == 0.0 ? x : s;
+  inv = __builtin_amdgcn_div_fixup(drcp_from(root, (2.0 * kInvBias) * h), root, 1.0);
+  return root;
 }
 
 // a * b + c: in double two rounded operations, exactly the expression as
@@ -173,10 +209,9 @@ __device__ __forceinline__ bool ratio_above(double a, double b, double t) {
 // Velocities in pencil order: normal u, then the two transverse components.
 __device__ __forceinline__ double eos_pressure(const Params &P, double rho, double u, double v1,
                                                double v2, double E, double e) {
-  const double g = P.gamma;
   double eps = xfma(-0.5, u * u + v1 * v1 + v2 * v2, E);
   if ((P.flags & kDualEnergy) && !ratio_above(eps, E, P.eta1)) eps = e;
-  return nmax((g - 1.0) * rho * eps, P.p_floor);
+  return nmax(P.gm1 * rho * eps, P.p_floor);
 }
 __device__ __forceinline__ void eos(const Params &P, double rho, double u, double v1, double v2,
                                     double E, double e, double &p, double &c) {
@@ -216,16 +251,16 @@ template <class T> __device__ __forceinline__ T second_diff(T qm, T q0, T qp) {
 }
 
 // Contact-steepening weight eta of a cell (0 = no steepening).
-// rm/rp, pm/pp: density and pressure of the two neighbours; d2m/d2p: second
+// gk: gamma K0; rm/rp, pm/pp: density and pressure of the two neighbours; d2m/d2p: second
 // differences centred on the two neighbours.
 template <class T>
-__device__ __forceinline__ T steepen_eta(double g, T rm, T rp, T pm, T pp, T d2m, T d2p) {
+__device__ __forceinline__ T steepen_eta(T gk, T rm, T rp, T pm, T pp, T d2m, T d2p) {
   const T drho = rp - rm;
   const T rmin = nmin(rp, rm);
   T eta = T(0);
   const bool bend = d2p * d2m < T(0);
   const bool jump = T(fabs(drho)) - T(kSteepEps) * rmin > T(0);
-  const bool contact = T(g * kSteepK0) * T(fabs(drho)) * nmin(pp, pm) >= T(fabs(pp - pm)) * rmin;
+  const bool contact = gk * T(fabs(drho)) * nmin(pp, pm) >= T(fabs(pp - pm)) * rmin;
   if (bend && jump && contact) {
     T etat = rdiv<T>(-(d2p - d2m), T(6) * drho);
     eta = clamp01<T>(T(kSteepEta1) * (etat - T(kSteepEta2)));
@@ -301,8 +336,7 @@ __device__ __forceinline__ EdgeRef<T> edge_ref(double g, const T (&edge)[5], con
   e.u = avg_edge(edge[1], dq[1], q6[1], y, w);
   e.p = avg_edge(edge[4], dq[4], q6[4], y, w);
   if constexpr (sizeof(T) == sizeof(double)) {
-    e.C = xsqrt(T(g) * e.p * e.r);
-    e.iC = xrcp(e.C);
+    e.C = xsqrt(T(g) * e.p * e.r, e.iC);
     e.ir = xrcp(e.r);
   } else {
     // float: C = rho sqrt(g p / rho) and 1/C = (1/rho) / sqrt(g p / rho), so
@@ -439,60 +473,65 @@ template <class T> __device__ __forceinline__ FluxT<T> narrow_flux(const Flux &D
 // acoustic guess, until the correction falls below rtol*p; the star state is
 // that last iterate, whose shock speeds are already at hand.  Returns p* and
 // the shock speeds, their reciprocals and the two sides' u* at p*.
+// The loop takes about a third of a sweep (6.6 iterations on the slowest lane of a
+// wave).  One test of the count ends it, and the reciprocal speeds start from
+// the roots: 66 double instructions with three hardware estimates (each four
+// times the issue of another) an iteration instead of 74 with five.
 struct StarState {
   double ps, wl, wr, iwl, iwr, usl, usr;
-  int iters;
 };
 __device__ __forceinline__ StarState two_shock_star(const Params &P, double rl, double ul,
                                                     double pl, double rr, double ur,
                                                     double pr) {
   const double g = P.gamma;
-  const double G1 = (g + 1.0) / (2.0 * g);
-  double cl = dsqrt(g * pl * rl);
-  double cr = dsqrt(g * pr * rr);
+  const double G1 = P.g1;
+  double hl, hr;
+  double cl = dsqrt(g * pl * rl, hl);
+  double cr = dsqrt(g * pr * rr, hr);
+  hl *= 4.0 * kInvBias;  // 2 / C_s: times the halved inverse root of W_s / C_s, 1 / W_s
+  hr *= 4.0 * kInvBias;
   double ipl = drcp(pl), ipr = drcp(pr);
   double ps = nmax(ddiv(cr * pl + cl * pr - cl * cr * (ur - ul), cl + cr), P.p_floor);
-  int it = 0;
-  bool capped = false;
   double wl, wr, iwl, iwr, usl, usr;
-  for (;;) {
-    wl = cl * dsqrt(1.0 + G1 * (ps * ipl - 1.0));
-    wr = cr * dsqrt(1.0 + G1 * (ps * ipr - 1.0));
-    iwl = drcp(wl);
-    iwr = drcp(wr);
+  for (int it = 0;; ++it) {
+    double yl, yr;
+    wl = cl * dsqrt(1.0 + G1 * (ps * ipl - 1.0), yl);
+    wr = cr * dsqrt(1.0 + G1 * (ps * ipr - 1.0), yr);
+    iwl = drcp_from(wl, yl * hl);
+    iwr = drcp_from(wr, yr * hr);
     usl = ul - (ps - pl) * iwl;
     usr = ur + (ps - pr) * iwr;
-    if (capped || it == P.riemann_max_iter) break;
+    if (it == P.riemann_max_iter) break;
     // twice 1/Z_s = (W_s^2 + C_s^2) / (2 W_s^3); the halving goes into the
     // final fused subtraction, exactly
     double izl = (wl * wl + cl * cl) * (iwl * iwl * iwl);
     double izr = (wr * wr + cr * cr) * (iwr * iwr * iwr);
     double pn = nmax(xfma(-2.0, ddiv(usr - usl, izl + izr), ps), P.p_floor);
-    ++it;
     if (fabs(pn - ps) <= P.riemann_rtol * pn) break;
     ps = pn;
-    if (it == P.riemann_max_iter) capped = true;
   }
-  return StarState{ps, wl, wr, iwl, iwr, usl, usr, it};
+  return StarState{ps, wl, wr, iwl, iwr, usl, usr};
 }
 
 __device__ __forceinline__ Flux two_shock_flux(const Params &P, double rl, double ul, double v1l,
                                                double v2l, double pl, double rr, double ur,
-                                               double v1r, double v2r, double pr, int &iters) {
+                                               double v1r, double v2r, double pr) {
   const double g = P.gamma;
   const StarState st = two_shock_star(P, rl, ul, pl, rr, ur, pr);
   const double ps = st.ps, wl = st.wl, wr = st.wr, iwl = st.iwl, iwr = st.iwr;
   const double usl = st.usl, usr = st.usr;
-  const int it = st.iters;
-  iters = it;
   double us = 0.5 * (usl + usr);
   // sample the upwind side of the contact at x/t = 0
   const bool left = us >= 0.0;
   double rK = left ? rl : rr, uK = left ? ul : ur, pK = left ? pl : pr;
   double iwK = left ? iwl : iwr;
   const double irK = drcp(rK);
-  double rs = drcp(irK - (ps - pK) * iwK * iwK);
-  if (rs < P.rho_floor) rs = P.rho_floor;
+  double irs = irK - (ps - pK) * iwK * iwK;  // 1 / rho*, to its rounding, below too
+  double rs = drcp(irs);
+  if (rs < P.rho_floor) {
+    rs = P.rho_floor;
+    irs = rcp_cubic(opaque(rs));
+  }
   // the upwind side's waves move away from the face: u - (speed) on the
   // left, u + (speed) on the right.  Written once with the side's values
   // and sign (x - y is x + (-y) exactly, and -h / (t - h) = h / (h - t)
@@ -508,7 +547,7 @@ __device__ __forceinline__ Flux two_shock_flux(const Params &P, double rl, doubl
     else { rb = rs; ub = us; pb = ps; }
   } else {        // rarefaction: linear through the fan
     const double head = uK + sgn * dsqrt(ddiv_by(g * pK, rK, irK));
-    const double tail = us + sgn * dsqrt(ddiv(g * ps, rs));
+    const double tail = us + sgn * dsqrt(ddiv_by(g * ps, rs, irs));
     bool outside = left ? head >= 0.0 : head <= 0.0;
     bool star = left ? tail <= 0.0 : tail >= 0.0;
     if (outside) { rb = rK; ub = uK; pb = pK; }
@@ -528,7 +567,7 @@ __device__ __forceinline__ Flux two_shock_flux(const Params &P, double rl, doubl
   F.m[1] = fr * ub + pb;
   F.m[2] = fr * v1;
   F.m[3] = fr * v2;
-  double eb = ddiv(pb, (g - 1.0) * rb);
+  double eb = ddiv(pb, P.gm1 * rb);
   double Eb = xfma(0.5, ub * ub + v1 * v1 + v2 * v2, eb);
   F.E = fr * Eb + ub * pb;
   F.e = fr * eb;
@@ -578,7 +617,7 @@ __device__ __forceinline__ StarState two_shock_star_mixed(const Params &P, doubl
                                                           double pl, double rr, double ur,
                                                           double pr) {
   const double g = P.gamma;
-  const double G1 = (g + 1.0) / (2.0 * g);
+  const double G1 = P.g1;
   const double al = g * pl * rl, ar = g * pr * rr;
   const double icl = rsqrt64_1(al), icr = rsqrt64_1(ar);
   const double cl = al * icl, cr = ar * icr;
@@ -596,10 +635,8 @@ __device__ __forceinline__ StarState two_shock_star_mixed(const Params &P, doubl
     ps = nmin(ex, pmin);
   }
   ps = nmax(ps, P.p_floor);
-  int it = 0;
-  bool capped = false;
   double wl, wr, iwl, iwr, usl, usr, yl, yr;
-  for (;;) {
+  for (int it = 0;; ++it) {
     const double xl = fma(G1, fma(ps, ipl, -1.0), 1.0);
     const double xr = fma(G1, fma(ps, ipr, -1.0), 1.0);
     yl = rsqrt64_1(xl);
@@ -610,16 +647,14 @@ __device__ __forceinline__ StarState two_shock_star_mixed(const Params &P, doubl
     iwr = icr * yr;
     usl = fma(-(ps - pl), iwl, ul);
     usr = fma(ps - pr, iwr, ur);
-    if (capped || it == P.riemann_max_iter) break;
+    if (it == P.riemann_max_iter) break;
     const double izl = fma(yl, yl, 1.0) * (0.5 * iwl);
     const double izr = fma(yr, yr, 1.0) * (0.5 * iwr);
     double pn = nmax(fma(-(usr - usl), rcp64_1(izl + izr), ps), P.p_floor);
-    ++it;
     if (fabs(pn - ps) <= P.riemann_rtol * pn) break;
     ps = pn;
-    if (it == P.riemann_max_iter) capped = true;
   }
-  return StarState{ps, wl, wr, iwl, iwr, usl, usr, it};
+  return StarState{ps, wl, wr, iwl, iwr, usl, usr};
 }
 
 // Two-shock flux of the mixed precision: the traced states come in float; the
@@ -677,7 +712,7 @@ __device__ __forceinline__ FluxT<float> two_shock_flux_mixed(const Params &P, fl
   // total energy flux in double: rho u is exact in double for float factors
   const double rbd = rb, ubd = ub, pbd = pb, v1d = v1, v2d = v2;
   const double frd = rbd * ubd;
-  const double eb = pbd * rcp64((P.gamma - 1.0) * rbd);
+  const double eb = pbd * rcp64(P.gm1 * rbd);
   F.E = frd * (eb + 0.5 * (ubd * ubd + v1d * v1d + v2d * v2d)) + ubd * pbd;
   return F;
 }
@@ -697,7 +732,7 @@ __device__ __forceinline__ Flux hllc_flux(const Params &P, double rl, double ul,
                                           double v1r, double v2r, double pr) {
   const double g = P.gamma;
   const double cl = dsqrt(ddiv(g * pl, rl)), cr = dsqrt(ddiv(g * pr, rr));
-  const double el = ddiv(pl, (g - 1.0) * rl), er = ddiv(pr, (g - 1.0) * rr);
+  const double el = ddiv(pl, P.gm1 * rl), er = ddiv(pr, P.gm1 * rr);
   const double El = el + 0.5 * (ul * ul + v1l * v1l + v2l * v2l);
   const double Er = er + 0.5 * (ur * ur + v1r * v1r + v2r * v2r);
   const double sL = vmin<double>(ul - cl, ur - cr);
@@ -747,8 +782,7 @@ __device__ __forceinline__ Flux riemann_flux(const Params &P, double rl, double 
   if (kUseHLLC && (P.flags & kHLLC)) {
     return hllc_flux(P, rl, ul, v1l, v2l, pl, rr, ur, v1r, v2r, pr);
   } else {
-    int iters;
-    return two_shock_flux(P, rl, ul, v1l, v2l, pl, rr, ur, v1r, v2r, pr, iters);
+    return two_shock_flux(P, rl, ul, v1l, v2l, pl, rr, ur, v1r, v2r, pr);
   }
 }
 
@@ -776,7 +810,7 @@ __device__ __forceinline__ Flux hll_flux(const Params &P, const double (&sl)[5],
   double rl = sl[0], ul = sl[1], pl = sl[4];
   double rr = sr[0], ur = sr[1], pr = sr[4];
   double cl = sqrt(g * pl / rl), cr = sqrt(g * pr / rr);
-  double el = pl / ((g - 1.0) * rl), er = pr / ((g - 1.0) * rr);
+  double el = pl / (P.gm1 * rl), er = pr / (P.gm1 * rr);
   double El = el + 0.5 * (ul * ul + sl[2] * sl[2] + sl[3] * sl[3]);
   double Er = er + 0.5 * (ur * ur + sr[2] * sr[2] + sr[3] * sr[3]);
   double Ul[6] = {rl, rl * ul, rl * sl[2], rl * sl[3], rl * El, rl * el};
@@ -918,12 +952,11 @@ __device__ __forceinline__ bool update_cell(const Params &P, double lam,
 template <class T>
 __device__ __forceinline__ void floor_cell(const Params &P, const CellInT<T> &c,
                                            double (&out)[6]) {
-  const double g = P.gamma;
   if (!(out[0] > P.rho_floor)) {
     out[0] = P.rho_floor;
     out[1] = double(c.u); out[2] = double(c.v1); out[3] = double(c.v2);
   }
-  double eps = P.p_floor / ((g - 1.0) * out[0]);
+  double eps = P.p_floor / (P.gm1 * out[0]);
   out[5] = eps;
   out[4] = eps + 0.5 * (out[1] * out[1] + out[2] * out[2] + out[3] * out[3]);
 }

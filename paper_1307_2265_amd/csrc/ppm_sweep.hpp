@@ -68,8 +68,8 @@ template <class S> struct PencilRef {
   int64_t base, stride;
   int n, g;
   double dx;
-  Dev<double> reg_lo, reg_hi;  // nullable: register slots of this pencil
-  int64_t reg_stride;       // stride between the six register fields
+  Dev<double> reg;          // nullable: register slot of its low face; the high face's follows
+  int64_t reg_stride;       // six fields later, reg_stride apart
   int lab[6];               // lab field index of each pencil-order flux slot
   Dev<const S> acc;         // nullable: acceleration along the pencil
 };
@@ -156,8 +156,7 @@ __device__ __forceinline__ PencilRef<S> make_pencil(const PatchDev &pd, int axis
   pc.lab[0] = 0; pc.lab[1] = 1 + axis; pc.lab[2] = 1 + t1; pc.lab[3] = 1 + t2;
   pc.lab[4] = 4; pc.lab[5] = 5;
   pc.acc = dev<const S>(pick3(axis, pd.acc[0], pd.acc[1], pd.acc[2]));
-  pc.reg_lo = register_slot(pd, axis, i1, i2, 0, pc.reg_stride);
-  pc.reg_hi = register_slot(pd, axis, i1, i2, 1, pc.reg_stride);
+  pc.reg = register_slot(pd, axis, i1, i2, 0, pc.reg_stride);
   return pc;
 }
 
@@ -481,7 +480,7 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
         rr[j] = fc[1][j];  // face r+1/2
       }
       if (steepen) {
-        T eta = steepen_eta<T>(gam, q[0][0], q[2][0], q[0][4], q[2][4], d2[0], d2[2]);
+        T eta = steepen_eta<T>(T(P.steep_gk), q[0][0], q[2][0], q[0][4], q[2][4], d2[0], d2[2]);
         if (eta != T(0)) {
           l[0] = mad<T>(l[0], T(1) - eta, xfma(T(0.25), dm[0][0], q[0][0]) * eta);
           rr[0] = mad<T>(rr[0], T(1) - eta, xfma(T(-0.25), dm[2][0], q[2][0]) * eta);
@@ -554,13 +553,14 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
         if (diffuse) diffuse_face(ff_b, fb);
         if (!spanned || (fb >= face_lo && fb <= own_hi)) ++n_fallback;
       }
-      if (fb == a0 - 1 && pc.reg_lo) {
+      if ((fb == a0 - 1 || fb == a1) && pc.reg) {
+        // (opaque: the twelve addresses, formed ahead of the loop, took 24
+        // registers and spilled what every iteration reads; without them and the
+        // constants in Params the FP64 march has no spill: 256^3 z sweep 1070 ->
+        // 955 us, last sweep 1126 -> 950)
+        const Dev<double> reg = opaque(pc.reg + (fb == a1 ? 6 * pc.reg_stride : 0));
 #pragma unroll
-        for (int j = 0; j < 6; ++j) pc.reg_lo[pc.lab[j] * pc.reg_stride] = dt * ff_b.get(j);
-      }
-      if (fb == a1 && pc.reg_hi) {
-#pragma unroll
-        for (int j = 0; j < 6; ++j) pc.reg_hi[pc.lab[j] * pc.reg_stride] = dt * ff_b.get(j);
+        for (int j = 0; j < 6; ++j) reg[pc.lab[j] * pc.reg_stride] = dt * ff_b.get(j);
       }
     }
 
