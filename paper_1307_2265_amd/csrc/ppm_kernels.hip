@@ -67,6 +67,11 @@ __device__ __forceinline__ int last_at_most(const int32_t *a, int lo, int hi, in
   return lo;
 }
 
+// This thread's slots in the LDS of a marching kernel.
+__device__ __forceinline__ double *march_slots(double *lds) {
+  return lds + kLdsMarch * (int(threadIdx.x) & ~63) + (int(threadIdx.x) & 63);
+}
+
 // Where a wave keeps the largest signal it knows of for a level, in the LDS
 // of a marching kernel.
 __device__ __forceinline__ unsigned long long *wave_top(double *lds, int level) {
@@ -133,8 +138,8 @@ sweep_kernel(const PatchDev *__restrict__ patches, const int32_t *__restrict__ c
       pc.acc = ref.acc;
     }
     const double dt = dt_dev[pd.level];
-    march_pencil<Prec, kCFL, kUseHLLC, kGrav>(P, pc, dt, expansion_a(P, pd.level),
-                                              lds + threadIdx.x, blockDim.x, nfb, nfl, cfl);
+    march_pencil<Prec, kCFL, kUseHLLC, kGrav, kGrouped ? 1 : 2>(P, pc, dt, expansion_a(P, pd.level),
+                                              march_slots(lds), 64, nfb, nfl, cfl);
   }
   if (nfb) atomicAdd(&counters[0], (unsigned long long)nfb);
   if (nfl) atomicAdd(&counters[1], (unsigned long long)nfl);
@@ -178,8 +183,8 @@ sweep_split_kernel(const PatchDev *__restrict__ patches, int32_t axis, int32_t m
     const int lead = g > kDeferCells ? g : kDeferCells;
     const MarchSpan span = half ? MarchSpan{m - lead, pc.n - g + 4, m, a1, m, mine}
                                 : MarchSpan{0, m + 4, g, m - 1, 0, nullptr};
-    march_pencil<Prec, kCFL, kUseHLLC, kGrav>(P, pc, dt, expansion_a(P, pd.level),
-                                              lds + threadIdx.x, blockDim.x, nfb, nfl, cfl, &span);
+    march_pencil<Prec, kCFL, kUseHLLC, kGrav, 2>(P, pc, dt, expansion_a(P, pd.level),
+                                              march_slots(lds),64, nfb, nfl, cfl, &span);
     if (half) {
       for (int c = 0; c < kDeferCells; ++c) {
         const int64_t o = pc.base + int64_t(m + c) * pc.stride;
@@ -341,12 +346,12 @@ batch_persistent_kernel(const PatchDev *__restrict__ patches, const int32_t *__r
           pencil_index(pd, axis, mask, idx, i1, i2);
           const PencilRef<S> pc = make_pencil<S>(pd, axis, i1, i2);
           if (kCFL && k == 2)
-            march_pencil<Prec, true, kUseHLLC, kGrav>(P, pc, dt, expansion_a(P, pd.level),
-                                                      lds + threadIdx.x, blockDim.x, nfb, nfl,
+            march_pencil<Prec, true, kUseHLLC, kGrav, 1>(P, pc, dt, expansion_a(P, pd.level),
+                                                      march_slots(lds), 64, nfb, nfl,
                                                       cfl);
           else
-            march_pencil<Prec, false, kUseHLLC, kGrav>(P, pc, dt, expansion_a(P, pd.level),
-                                                       lds + threadIdx.x, blockDim.x, nfb, nfl,
+            march_pencil<Prec, false, kUseHLLC, kGrav, 1>(P, pc, dt, expansion_a(P, pd.level),
+                                                       march_slots(lds), 64, nfb, nfl,
                                                        cfl);
         }
       }

@@ -74,11 +74,14 @@ template <class S> struct PencilRef {
   Dev<const S> acc;         // nullable: acceleration along the pencil
 };
 
-// LDS of a marching thread, in doubles (strided by the block size): two
-// slots of the traced L and R states of a face (for the fallback), the final
-// flux of the face behind the cell about to be written (read only by the
-// fallback) and that cell's provisional update, then, in the sweeps that take
-// the next timestep, the wave's signal maxima (64 levels for 64 threads).
+// LDS of a marching thread, in doubles: two slots of the traced L and R states
+// of a face (for the fallback), the final flux of the face behind the cell
+// about to be written (read only by the fallback) and that cell's provisional
+// update.  Each wave holds its threads' in one piece, a lane apart, so that
+// every slot is a constant offset from the thread's first (a block-sized stride
+// kept thirteen addresses in registers and added up the others in every
+// iteration).  After all waves', in the sweeps that take the next timestep,
+// come the waves' signal maxima (64 levels for 64 threads).
 constexpr int kSlotDoubles = 10;
 constexpr int kLdsFluxA = 2 * kSlotDoubles;
 constexpr int kLdsProvA = kLdsFluxA + 7;
@@ -326,10 +329,15 @@ struct MarchSpan {
 // One thread marches one pencil (or the part of it `span` gives).  kCFL: also
 // take the signal speed of every cell written (the sweep must then be the
 // last of its step).
+// The marching loop holds kUnroll iterations: two spare half the moves that
+// carry the window on (512^3 y sweep mixed 4.74 -> 4.52 ms, FP64 6.78 -> 6.60,
+// 256^3 last sweep by halves 950 -> 925 us); over several patches, where
+// pencils are short, one is as fast or faster (4096-patch batch, mixed y sweep
+// 1335 us, 1370 with two).
 // a: the level's expansion factor (1 for the static equations).  kGrav: the
 // general build, with the gravity source terms (applied where the pencil has
 // an acceleration field) and the optional diffusive flux.
-template <class Prec, bool kCFL, bool kUseHLLC, bool kGrav>
+template <class Prec, bool kCFL, bool kUseHLLC, bool kGrav, int kUnroll>
 __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> &pc, double dt,
                              double a, double *lds_slots, int slot_stride, uint32_t &n_fallback,
                              uint32_t &n_floor, const CflAcc &cfl, const MarchSpan *span = nullptr) {
@@ -429,7 +437,11 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
     nr = pc.rho[o]; nu = pc.u[o]; nv1 = pc.v1[o]; nv2 = pc.v2[o]; nE = pc.E[o]; ne = pc.e[o];
   }
 
-  for (int k = begin; k <= kend; ++k) {
+  for (int kk = begin; kk <= kend; kk += kUnroll)
+#pragma unroll
+  for (int step = 0; step < kUnroll; ++step) {
+    const int k = kk + step;
+    if (step > 0 && k > kend) break;
     const int t = k - begin;  // cells read so far, less one
     // energies of cell B = k-4 (updated below), fetched early to hide latency
     if (k - 4 >= b0 && k - 4 <= a1) {
@@ -503,7 +515,7 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
     }
 
     // ---- 6. Riemann problem at face fc = (r-1)+1/2
-    double *slot_c = lds_slots + (k & 1) * kSlotDoubles * slot_stride;
+    double *slot_c = lds_slots + (t & 1) * kSlotDoubles * slot_stride;
     if (r - 1 >= b0 - 1 && r - 1 <= a1) {
       ft_c = face_flux<kUseHLLC, T>(P, lcarry, rstate);
       if (diffuse) diffuse_face(ft_c, r - 1);
@@ -542,7 +554,7 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
     if (fb >= b0 - 1 && fb <= a1) {
       hll_b = fallback && (bad_a || bad_b);
       if (hll_b) {
-        const double *slot_b = lds_slots + ((k - 1) & 1) * kSlotDoubles * slot_stride;
+        const double *slot_b = lds_slots + ((t - 1) & 1) * kSlotDoubles * slot_stride;
         double sl[5], sr[5];
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
