@@ -149,7 +149,7 @@ sweep_kernel(const PatchDev *__restrict__ patches, const int32_t *__restrict__ c
 // The marching sweep of one patch with two threads per pencil, for sweeps
 // with too few pencils to give every SIMD two waves: lanes 0-31 of a wave
 // march the first halves of 32 consecutive pencils and lanes 32-63 the second
-// halves, from max(5, g) cells before their first own cell (see MarchSpan).
+// halves, from max(5, g + 1) cells before their first own cell (see MarchSpan).
 // The second half stores its first five cells only after its march, from
 // `defer` (30 doubles per pencil): the first half reads them as input at the
 // end of its own march, and the wave leaves the march loop only when both
@@ -178,9 +178,11 @@ sweep_split_kernel(const PatchDev *__restrict__ patches, int32_t axis, int32_t m
     const int g = pc.g, a1 = pc.n - g - 1;
     const int m = g + (pc.n - 2 * g + 1) / 2;  // first cell of the second half
     double *mine = defer + int64_t(idx) * (kDeferCells * 6);
-    // the second half starts at least five cells, and at least g, before its
-    // first own cell (its first g cells are its ghosts)
-    const int lead = g > kDeferCells ? g : kDeferCells;
+    // the second half starts at least five cells before its first own cell, and
+    // at least g + 1: its first g cells are its ghosts, and the face before its
+    // own cells takes the fallback's flux where the cell before them goes bad,
+    // which therefore has to be one it updates
+    const int lead = g + 1 > kDeferCells ? g + 1 : kDeferCells;
     const MarchSpan span = half ? MarchSpan{m - lead, pc.n - g + 4, m, a1, m, mine}
                                 : MarchSpan{0, m + 4, g, m - 1, 0, nullptr};
     march_pencil<Prec, kCFL, kUseHLLC, kGrav, 2>(P, pc, dt, expansion_a(P, pd.level),

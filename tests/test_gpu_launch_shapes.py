@@ -87,3 +87,31 @@ def test_several_patches_step(P, O, npatch, tiles):
             assert np.array_equal(out[k], getattr(G, k)), k
         assert np.array_equal(p.flux_reg.cpu().numpy(), G.flux_reg)
     plan.close()
+
+
+@pytest.mark.parametrize("n", [16, 17, 18, 19, 40, 41])
+@pytest.mark.parametrize("ghost", [3, 4, 5, 6])
+@pytest.mark.parametrize("tiles", ["lanes=0", "lanes=0 split=0"])
+def test_marching_by_halves_at_odd_and_even_lengths(P, O, n, ghost, tiles):
+    # two iterations to a round: either half of a pencil may end in the middle of
+    # one, next to the cells the other half owns; fluxes and event counts too
+    import torch
+    d = W.random_grid(n, n + 1, n + 2, 6500 + n + ghost, W.SHOCKED, ghost=ghost)
+    G = oracle_grid(O, d, ghost=ghost, dx=(1.0, 0.5, 0.25), with_reg=True)
+    patch = to_device(d, P.PPM_FP64, ghost=ghost, dx=(1.0, 0.5, 0.25), with_reg=True)
+    plan = P.Plan([patch], 1, P.PPM_FP64, P.params(), tile_config=tiles)
+    dt = _dt(2e-3)
+    fb = fl = 0
+    for s in (0, 1):
+        O.fill_periodic(G)
+        c = O.step(G, O.params(), 2e-3, s)
+        fb, fl = fb + c.fallback_faces, fl + c.floored_cells
+        plan.ppm_fill_periodic()
+        plan.ppm_step(dt, s)
+    torch.cuda.synchronize()
+    out = from_device(patch)
+    for f in FIELDS:
+        assert np.array_equal(out[f], getattr(G, f)), f
+    assert np.array_equal(patch.flux_reg.cpu().numpy(), G.flux_reg)
+    assert plan.ppm_event_counts() == (fb, fl)
+    plan.close()
