@@ -437,11 +437,16 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
     nr = pc.rho[o]; nu = pc.u[o]; nv1 = pc.v1[o]; nv2 = pc.v2[o]; nE = pc.E[o]; ne = pc.e[o];
   }
 
+  // The last round of two may hold one iteration too many.  Marching by halves it
+  // is run (256^3 y sweep 972 -> 922 us, mixed 700 -> 686): it reads cells of the
+  // patch only, and neither counts nor writes, the cell it would finish not
+  // being an owned one.  The FP64 build that takes the timestep would spill, and
+  // leaves the loop instead (925 us against 1014), as the whole march does (the same).
   for (int kk = begin; kk <= kend; kk += kUnroll)
 #pragma unroll
   for (int step = 0; step < kUnroll; ++step) {
     const int k = kk + step;
-    if (step > 0 && k > kend) break;
+    if (step > 0 && k > kend && !(spanned && (!kCFL || !kExactP))) break;
     const int t = k - begin;  // cells read so far, less one
     // energies of cell B = k-4 (updated below), fetched early to hide latency
     if (k - 4 >= b0 && k - 4 <= a1) {
