@@ -90,9 +90,9 @@ struct ppm_amr {
   double *d_acc = nullptr;
   std::vector<int64_t> acc_off;                // per patch (-1 on the root)
   ppm::AccItem *d_accitems = nullptr;
-  int64_t *d_accprefix = nullptr;
+  int32_t *d_accfirst = nullptr;
   std::vector<int32_t> acc_beg;                // per level: first item (nlevels + 1)
-  std::vector<int64_t> acc_total;              // per level: values summed
+  std::vector<int32_t> acc_total;              // per level: blocks of the sum
   std::vector<int64_t> acc_span;               // per level: its registers' whole block
   // flux correction, per coarse level
   ppm::CorrTarget *d_targets = nullptr;
@@ -124,7 +124,7 @@ void destroy(ppm_amr *h) {
   for (void *b : h->old_bufs) (void)hipFree(b);
   for (void *b : h->blend_bufs) (void)hipFree(b);
   void *bufs[] = {h->d_dt,   h->d_cfl,      h->d_old,       h->d_blend,   h->d_cap,
-                  h->d_rows, h->d_acc,      h->d_accitems,  h->d_accprefix, h->d_targets,
+                  h->d_rows, h->d_acc,      h->d_accitems,  h->d_accfirst, h->d_targets,
                   h->d_contribs, h->d_proj, h->d_projprefix, h->d_need,   h->d_needprefix};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
@@ -280,7 +280,7 @@ ppm_status evolve(ppm_amr *h, int l, double t_end, bool has_end, hipStream_t s) 
     if ((st = step_level(h, l, order, again && !h->expand, s)) != PPM_OK) return st;
     if (l > 0 && h->acc_total[l] > 0) {
       const int32_t i0 = h->acc_beg[l], ni = h->acc_beg[l + 1] - i0;
-      e = ppm::launch_accumulate(h->d_accitems + i0, h->d_accprefix + i0 + l, ni,
+      e = ppm::launch_accumulate(h->d_accitems + i0, h->d_accfirst + i0 + l, ni,
                                  h->acc_total[l], s);
       if (e != hipSuccess) return hip_fail(e, "register sum launch");
     }
@@ -433,11 +433,12 @@ ppm_status build_lists(ppm_amr *h) {
   h->acc_span.assign(size_t(L) + 1, 0);
   std::vector<int64_t> acc_item_off;       // offset of each item's sum in d_acc
   std::vector<const double *> acc_item_reg;
-  std::vector<int64_t> accprefix;
+  std::vector<int64_t> acc_item_n;
+  std::vector<int32_t> accfirst;
   // (only the faces that a correction reads are summed)
   for (int l = 0; l < L; ++l) {
     h->acc_beg[l] = int32_t(acc_item_off.size());
-    int64_t run = 0;
+    int32_t run = 0;
     for (int32_t p : h->members[l]) {
       if (l == 0) continue;
       const ppm_patch &q = h->patches[p];
@@ -449,13 +450,14 @@ ppm_status build_lists(ppm_amr *h) {
         const int64_t f1 = reg_face_offset(q.nx, q.ny, q.nz, face + 1);
         acc_item_off.push_back(acc_total + f0);
         acc_item_reg.push_back(q.flux_reg + f0);
-        accprefix.push_back(run);
-        run += f1 - f0;
+        acc_item_n.push_back(f1 - f0);
+        accfirst.push_back(run);
+        run += int32_t((f1 - f0 + ppm::kAccBlock - 1) / ppm::kAccBlock);
       }
       acc_total += n;
       h->acc_span[l] += n;
     }
-    accprefix.push_back(run);
+    accfirst.push_back(run);
     h->acc_total[l] = run;
   }
   h->acc_beg[L] = int32_t(acc_item_off.size());
@@ -466,9 +468,10 @@ ppm_status build_lists(ppm_amr *h) {
   }
   std::vector<ppm::AccItem> accitems;
   for (size_t i = 0; i < acc_item_off.size(); ++i)
-    accitems.push_back(ppm::AccItem{h->d_acc + acc_item_off[i], acc_item_reg[i]});
+    accitems.push_back(ppm::AccItem{h->d_acc + acc_item_off[i], acc_item_reg[i],
+                                    acc_item_n[i]});
   if ((e = upload(&h->d_accitems, accitems)) != hipSuccess ||
-      (e = upload(&h->d_accprefix, accprefix)) != hipSuccess)
+      (e = upload(&h->d_accfirst, accfirst)) != hipSuccess)
     return hip_fail(e, "register sum lists");
 
   // capture rows per (level, axis)

@@ -139,13 +139,17 @@ template <class Prec>
 hipError_t launch_capture(const PatchDev *patches, const CaptureRow *rows, int32_t nrows,
                           int32_t axis, const double *dt_dev, const Params &P, hipStream_t s);
 
-// acc[i] += reg[i] over the listed register blocks (prefix over their sizes).
+// acc[i] += reg[i], i < n, over the listed registers, in blocks of kAccBlock
+// values of one register: first[k] counts the blocks of the items before item k,
+// `blocks` those of all.
+constexpr int kAccBlock = 1024;
 struct AccItem {
   Dev<double> acc;
   Dev<const double> reg;
+  int64_t n;
 };
-hipError_t launch_accumulate(const AccItem *items, const int64_t *prefix, int32_t nitems,
-                             int64_t total, hipStream_t s);
+hipError_t launch_accumulate(const AccItem *items, const int32_t *first, int32_t nitems,
+                             int32_t blocks, hipStream_t s);
 
 // Flux correction: one coarse cell per target, its contributions applied in
 // list order.  A contribution is one face of a child footprint: the coarse
