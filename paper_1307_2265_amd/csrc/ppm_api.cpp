@@ -121,6 +121,42 @@ int64_t sweep_pencils(const PatchDev &d, int axis, int tm) {
   return w1 * w2;
 }
 
+// A marching sweep of np pencils of n cells in one patch, with `round` threads
+// to a round of one block per compute unit: whether two threads march each
+// pencil (half its cells and about 11 more each), and whether the threads past
+// the last whole round go to the lane-parallel kernel, one pencil per wave.
+// The cost is counted in cells a thread marches in turn.  A round takes
+// what its threads march, and 0.15 more where it has its compute units to
+// itself (one wave per SIMD: the last of an odd number of rounds); a pencil
+// in the tail costs 1.6 times its share of a marched round along y, 2.5
+// along z, whose lines lie furthest apart, 1.2 and 1.5 in the mixed precision.
+// Fitted to cubes of 264 to 450 cells, where the choice is the best or within 3 %
+// of it: FP64 y sweeps of 264 cells 1365 -> 1041 us, 320 2130 -> 1810, 380 3700 -> 2880,
+// 450 5680 -> 4800, against splitting whatever has fewer pencils than two rounds
+// and a tail of at most an eighth of one.
+MarchShape choose_march(int64_t np, int n, int axis, ppm_precision prec, int64_t round,
+                        bool may_split, bool may_tail) {
+  if (round <= 0) return MarchShape{false, false};
+  const double f64 = axis == 2 ? 2.5 : 1.6, mixed = axis == 2 ? 1.5 : 1.2;
+  const double lanes = prec == PPM_FP64 ? f64 : mixed;
+  MarchShape best{false, false};
+  double least = 0.0;
+  if (np >= 4 * round) may_split = false;  // little to gain, and 240 bytes a pencil to keep
+  for (int split = 0; split <= int(may_split); ++split) {
+    const double cells = split ? 0.5 * n + 11.0 : double(n);
+    const int64_t threads = (split ? 2 : 1) * np, whole = threads / round, rest = threads % round;
+    for (int tail = 0; tail <= int(may_tail && whole > 0 && rest > 0); ++tail) {
+      const int64_t rounds = whole + (rest > 0 && !tail);
+      const double cost = cells * (double(rounds) + (rounds % 2 ? 0.15 : 0.0)) +
+                          (tail ? lanes * n * double(rest / (split ? 2 : 1)) / double(round) : 0.0);
+      if ((split || tail) && !(cost < least)) continue;
+      least = cost;
+      best = MarchShape{split != 0, tail != 0};
+    }
+  }
+  return best;
+}
+
 // Longer runs pack pencils more tightly into 64-lane segments, shorter ones
 // give the device more waves: the choice minimises the segments of a run (and
 // the start of a wave, 0.15 of one) times the waves per SIMD (at least 1.3,
@@ -504,16 +540,8 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
         pl->nblocks[slot] = chunks[size_t(slot + 1) * stride - 1];
     }
   }
-  // One patch, few pencils: a marching sweep with fewer pencils than two
-  // blocks per compute unit leaves the device at one wave per SIMD or less,
-  // so two threads march each pencil (split; pencils of at least 16 active
-  // cells).  And marched threads just over a whole number of rounds of one
-  // block per compute unit: march the whole rounds and give the few pencils
-  // left (at most an eighth of a round) to the lane-parallel kernel, one
-  // pencil per wave, instead of a last round in which a few compute units
-  // march a block more than the others (a 256^3 y sweep: 262 blocks of 256
-  // on 256 compute units took 2.2 ms, the 256 blocks of its z sweep 1.55).
-  // A given tail_round replaces the round and the eighth rule (any rest).
+  // One patch: threads per pencil and the tail of every marching sweep.
+  // A given tail_round replaces the round and the choice of a tail (any rest).
   int64_t defer_pencils = 0;
   if (npatch == 1 && !pl->group && (cus > 0 || pl->tail_round > 0)) {
     for (int c = 0; c < 2; ++c) {
@@ -521,8 +549,14 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
         const int axis = slot / 4, tm = slot % 4;
         const PatchDev &d = pl->host[0];
         const int64_t np = ppm_detail::sweep_pencils(d, axis, tm);
-        const bool split = pl->split && cus > 0 && d.n[axis] >= 16 &&
-                           np < 2 * int64_t(cus) * pl->block;
+        const bool may_split = pl->split && cus > 0 && d.n[axis] >= 16;
+        const ppm_detail::MarchShape shape =
+            pl->tail_round ? ppm_detail::MarchShape{may_split && np < 2 * int64_t(cus) * pl->block,
+                                                    true}
+                           : ppm_detail::choose_march(np, d.n[axis] + 2 * d.ghost, axis, prec,
+                                                      int64_t(cus) * pl->block, may_split,
+                                                      pl->tail != 0);
+        const bool split = shape.split;
         const int64_t tpp = split ? 2 : 1, threads = tpp * np;
         // threads per round: tail_round pencils, else one block per compute unit
         const int64_t cap = pl->tail_round ? pl->tail_round * tpp : int64_t(cus) * pl->block;
@@ -533,7 +567,7 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
         }
         if (!pl->tail || cap <= 0) continue;
         const int64_t rest = threads % cap;
-        if (threads < cap || rest == 0 || (pl->tail_round == 0 && rest * 8 > cap)) continue;
+        if (threads < cap || rest == 0 || !shape.tail) continue;
         const int64_t waves = pl->lanes_block / 64;
         pl->tail_pencil0[c][slot] = int32_t((threads - rest) / tpp);
         pl->tail_main[c][slot] = int32_t((threads - rest) / pl->block);

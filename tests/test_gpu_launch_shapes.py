@@ -115,3 +115,31 @@ def test_marching_by_halves_at_odd_and_even_lengths(P, O, n, ghost, tiles):
     assert np.array_equal(patch.flux_reg.cpu().numpy(), G.flux_reg)
     assert plan.ppm_event_counts() == (fb, fl)
     plan.close()
+
+
+@pytest.mark.parametrize("dims", [(135, 70, 137), (70, 240, 139), (129, 129, 40)])
+@pytest.mark.parametrize("tiles", ["lanes=0 block=64", "lanes=1 block=64"])
+def test_halves_and_tails_as_a_plan_chooses_them(P, O, dims, tiles):
+    # rounds of 64-thread blocks: sweeps of less than one round, of a little and of
+    # more than half a round past a whole number of them, by halves and whole
+    import torch
+    nx, ny, nz = dims
+    d = W.random_grid(nx, ny, nz, 6700 + nx, W.SHOCKED)
+    dx = (1.0, 0.5, 0.25)
+    G = oracle_grid(O, d, dx=dx)
+    patch = to_device(d, P.PPM_FP64, dx=dx)
+    plan = P.Plan([patch], 1, P.PPM_FP64, P.params(), tile_config=tiles)
+    dt = _dt(2e-3)
+    for s in (0, 1):
+        O.fill_periodic(G)
+        O.step(G, O.params(), 2e-3, s)
+        want = O.cfl_dt(G, O.params())
+        plan.ppm_fill_periodic()
+        dt.fill_(2e-3)
+        plan.ppm_step_cfl(dt, s)
+        assert float(dt.item()) == want
+    torch.cuda.synchronize()
+    out = from_device(patch)
+    for f in FIELDS:
+        assert np.array_equal(out[f], getattr(G, f)), f
+    plan.close()
