@@ -183,21 +183,22 @@ int64_t ppm_flux_reg_size(int32_t nx, int32_t ny, int32_t nz);
  *                  patches 0.06 against 1.6 ms a step, 4096 7.4 against 8.4).
  *   batch_block=B  threads per workgroup of the persistent launch (64..256).
  *   batch_blocks=W workgroups of the persistent launch (default: 512/B per CU).
- *   tail=0|1       one ungrouped patch: when a marching sweep's pencils
+ *   tail=0|1       one ungrouped patch: when a marching sweep's threads
  *                  exceed a whole number of rounds of one marching block per
- *                  compute unit by at most an eighth of a round, march the
- *                  whole rounds and stream the rest with the lane-parallel
- *                  kernel, one pencil per wavefront, in a second launch
- *                  (default 1).
+ *                  compute unit and an estimate of the cost says so, march
+ *                  the whole rounds and stream the rest with the
+ *                  lane-parallel kernel, one pencil per wavefront, in a
+ *                  second launch (default 1; 0: never).
  *   tail_round=R   take R pencils (a multiple of block) as the round and give
  *                  any rest to the lane-parallel launch (for tests and tuning).
- *   split=0|1      one ungrouped patch: a marching sweep with fewer pencils
- *                  than two blocks per compute unit, of at least 16 active
- *                  cells each, runs two threads per pencil (each marches half
- *                  of it, from max(5, ghost) cells before its first own
- *                  cell), which
- *                  doubles the waves on a device the pencils cannot fill
- *                  (default 1).
+ *   split=0|1      one ungrouped patch: a marching sweep over pencils of at
+ *                  least 16 active cells runs two threads per pencil where
+ *                  the same estimate says so (each marches half of it, the
+ *                  second from max(5, ghost + 1) cells before its first own
+ *                  cell): more waves on a device the pencils cannot fill,
+ *                  or an even number of rounds (default 1; 0: never; with
+ *                  tail_round, whenever the pencils are fewer than two blocks
+ *                  per compute unit).
  * Results do not depend on the launch shapes.  Uploads the patch table to
  * the device on `hip_stream` (0 = default stream) and allocates the event
  * counters.  On success *out owns the plan. */

@@ -6,7 +6,7 @@
 //     thread of the block marches one pencil (ppm_sweep.hpp).  A single big
 //     grid is the one-patch case of the same kernel.
 //   * sweep_split_kernel: the marching sweep of one patch with two threads
-//     per pencil, when the pencils are too few to fill the device.
+//     per pencil, where that leaves the device less idle.
 //   * sweep_lanes_kernel: the same sweep with the cells of a pencil across
 //     the lanes of a wave (ppm_lanes.hpp), for x sweeps.
 //   * sweep_tail_kernel: the same lane-parallel code over the last pencils of

@@ -773,8 +773,8 @@ __device__ __forceinline__ Flux hllc_flux(const Params &P, double rl, double ul,
 // The face flux of the solver a kernel is built for: two-shock, or HLLC
 // (the flag kHLLC picks the kernel build at launch, so the two solvers'
 // launches are separate kernels).  The HLLC build keeps the two-shock path
-// behind the same flag: without it the FP64 marching loop is allocated with
-// 44 spilled registers instead of 16 and runs 30 % slower (measured).
+// behind the same flag: without it the FP64 marching loop, when it still spilled,
+// was allocated with 44 spilled registers instead of 16 and ran 30 % slower.
 template <bool kUseHLLC>
 __device__ __forceinline__ Flux riemann_flux(const Params &P, double rl, double ul, double v1l,
                                              double v2l, double pl, double rr, double ur,
