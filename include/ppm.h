@@ -162,8 +162,9 @@ int64_t ppm_flux_reg_size(int32_t nx, int32_t ny, int32_t nz);
  *                  (x only) and, unless tile_config sets one of lanes, block,
  *                  tail and tail_round, the y and z axes too where the patches
  *                  have too few pencils to fill the device one thread each:
- *                  ghosted transverse pencils below 208 (y) and 160 (z) x the
- *                  number of compute units for one patch, 416 for several.
+ *                  ghosted transverse pencils below 208 (y) and 110 (z; in the
+ *                  mixed precision 224 and 208) x the number of compute units
+ *                  for one patch, 416 for several.
  *   block=B        threads per block of the marching kernel (64..256;
  *                  default 256 for one patch, 64 for several).
  *   lanes_block=B  threads per block of the lane-parallel kernel (64..256;

@@ -204,19 +204,22 @@ int32_t choose_run_segments(const PatchDev *d, int32_t npatch, ppm_precision pre
 // A marching sweep gives each pencil to one thread (two in a plan of one
 // patch), so with few pencils its time is that of one march whatever their
 // number, while a lane-parallel sweep's falls with them.  Measured, FP64
-// (mixed), us a sweep: 64^3 y 39 lane-parallel, 186 marching; 128^3 157 and
-// 345; 192^3 y 526 and 798 (359 and 525), z 746 and 796 (367 and 522); 224^3 y
-// 865 and 938, z 1536 and 936; 256^3 y 1305 and 1167 (853 and 788).  A z
+// (mixed), us a sweep: 128^3 y 142 lane-parallel, 279 marching (111 and
+// 235); 208^3 y 592 and 640 (440 and 538), z 755 and 700 (457 and 548); 224^3 y
+// 762 and 799, z 1480 and 760 (703 and 708); 232^3 y 872 and 792 (617 and 730), z
+// (652 and 588); 240^3 y 958 and 824 (678 and 612); 160^3 z 262 and 359, 164^3 z
+// 396 and 372, 192^3 z 717 and 578.  A z
 // sweep's lanes lie a plane apart, hence its earlier end.  Several patches of
 // 8^3 .. 32^3, us a step: 12 patches 62 and 328, 100 (60 thousand pencils a
 // sweep) 262 and 413 (193 and 317), 300 (180 thousand) 798 and 712.
-int32_t default_lanes(const PatchDev *d, int32_t npatch, int cus) {
+int32_t default_lanes(const PatchDev *d, int32_t npatch, ppm_precision prec, int cus) {
   int64_t np[2] = {0, 0};
   for (int32_t i = 0; i < npatch; ++i)
     for (int a = 0; a < 2; ++a) np[a] += sweep_pencils(d[i], a + 1, 0);
   const int64_t c = cus;
-  return 1 | (np[0] < c * (npatch == 1 ? 208 : 416) ? 2 : 0) |
-         (np[1] < c * (npatch == 1 ? 160 : 416) ? 4 : 0);
+  const bool f64 = prec == PPM_FP64;
+  const int y = npatch > 1 ? 416 : (f64 ? 208 : 224), z = npatch > 1 ? 416 : (f64 ? 110 : 208);
+  return 1 | (np[0] < c * y ? 2 : 0) | (np[1] < c * z ? 4 : 0);
 }
 
 }  // namespace ppm_detail
@@ -434,7 +437,7 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pl->device) != hipSuccess)
     cus = 0;
-  if (!pl->lanes_set) pl->lanes_mask = ppm_detail::default_lanes(pl->host.data(), npatch, cus);
+  if (!pl->lanes_set) pl->lanes_mask = ppm_detail::default_lanes(pl->host.data(), npatch, prec, cus);
   // prefix arrays of work chunks
   const int stride = npatch + 1;
   std::vector<int32_t> chunks(size_t(25) * stride, 0);

@@ -197,7 +197,7 @@ extern "C" ppm_status ppm_step_cfl_noalloc(const ppm_patch *patches, int32_t npa
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     cus = 0;
   const int32_t block = npatch == 1 ? 256 : 64, lanes_block = block;
-  const int32_t lanes_mask = ppm_detail::default_lanes(host, npatch, cus);
+  const int32_t lanes_mask = ppm_detail::default_lanes(host, npatch, prec, cus);
   const int stride = npatch + 1;
   Shape shapes[3];
   std::memset(shapes, 0, sizeof shapes);

@@ -92,7 +92,7 @@ MarchShape choose_march(int64_t np, int n, int axis, ppm_precision prec, int64_t
                         bool may_split, bool may_tail);
 int32_t choose_run_segments(const PatchDev *d, int32_t npatch, ppm_precision prec, int axis,
                             int tm, int cus);
-int32_t default_lanes(const PatchDev *d, int32_t npatch, int cus);
+int32_t default_lanes(const PatchDev *d, int32_t npatch, ppm_precision prec, int cus);
 
 // A box [lo, hi) of cell indices.
 struct IBox {
