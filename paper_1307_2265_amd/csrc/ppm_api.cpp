@@ -111,6 +111,12 @@ ppm::Params device_params(ppm_precision prec, const ppm_params *p) {
     P.rho_floor = float_at_or_above(p->rho_floor);
     P.p_floor = float_at_or_above(p->p_floor);
   }
+  auto up = [](double x) {
+    return x > double(FLT_MAX) ? std::numeric_limits<float>::infinity()
+                               : float(float_at_or_above(x));
+  };
+  P.gg1_up = up(p->gamma * P.gm1);
+  P.gpf_up = up(p->gamma * P.p_floor);
   return P;
 }
 

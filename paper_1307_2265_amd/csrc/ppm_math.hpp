@@ -52,6 +52,9 @@ struct Params {
   // formed on the host, they reach the sweeps in scalar registers (formed in
   // the kernels they hold six vector registers over the whole march)
   double gm1, g1, steep_gk;
+  // gamma (gamma - 1) and gamma p_floor, rounded up (infinite beyond the float
+  // range): the float bound of a signal speed starts from them
+  float gg1_up, gpf_up;
 };
 
 // Expansion factor of a level (1 without expansion factors).

@@ -248,33 +248,45 @@ __device__ __forceinline__ void wave_raise(unsigned long long *p, unsigned long 
   __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
+// An upper bound of a cell's signal speed, velocities in pencil order, for
+// every state, gamma and cell width the interface takes; infinity or NaN where
+// float arithmetic gives none (the caller dismisses a cell only below a finite
+// bound).  Each float rounding is below 1e-7: E - ke, which may cancel, is raised
+// by 1e-6 of its terms (t), the whole by 1e-5.  What lies near or below the
+// smallest normal float is covered by absolute terms: 1e-38 on the internal
+// energy, 1e-36 on the squared sound speed, 1e-35 on the sum.  t enters the
+// squared sound speed once more, since with t infinite E - ke can be NaN, which
+// a maximum would drop.  gamma (gamma - 1) and gamma p_floor come from the host,
+// rounded up (formed here from a float gamma, the difference from one would be
+// lost for gamma near one: at 1.0005 the bound was 2.6e-5 low).
+__device__ __forceinline__ float signal_bound(const Params &P, const float (&inv)[3], float r,
+                                              float u, float v1, float v2, float E, float e) {
+  const float ke = 0.5f * __builtin_fmaf(u, u, __builtin_fmaf(v1, v1, v2 * v2));
+  const float t = fabsf(E) + ke;
+  const float eps = nmax(__builtin_fmaf(1e-6f, t, E - ke), e) + 1e-38f;
+  const float c2 = nmax(P.gg1_up * eps, P.gpf_up * __builtin_amdgcn_rcpf(r));
+  const float c = __builtin_amdgcn_sqrtf(c2 + __builtin_fmaf(1e-30f, t, 1e-36f));
+  const float s = __builtin_fmaf(c + fabsf(u), inv[0],
+                                 __builtin_fmaf(c + fabsf(v1), inv[1], (c + fabsf(v2)) * inv[2]));
+  // (a reciprocal density outside these limits may round to zero or overflow)
+  return r > 1e-30f && r < 1e30f ? __builtin_fmaf(s, 1.00001f, 1e-35f) : __builtin_inff();
+}
+
+// 1/dx for signal_bound; infinity, which gives no finite bound, for a width
+// whose reciprocal float arithmetic cannot hold to 1e-6.
+__device__ __forceinline__ float bound_inverse(double dx) {
+  return dx > 1e-30 && dx < 1e30 ? 1.0f / float(dx) : __builtin_inff();
+}
+
 __device__ __forceinline__ CflAcc cfl_acc(const PatchDev *pd, int axis,
                                           unsigned long long *global, unsigned long long *wave) {
   const int t1 = axis == 0 ? 1 : 0, t2 = axis == 2 ? 1 : 2;
   *wave = read_now(global);
   return CflAcc{axis, pd,
-                {1.0f / float(pick3(axis, pd->dx[0], pd->dx[1], pd->dx[2])),
-                 1.0f / float(pick3(t1, pd->dx[0], pd->dx[1], pd->dx[2])),
-                 1.0f / float(pick3(t2, pd->dx[0], pd->dx[1], pd->dx[2]))},
+                {bound_inverse(pick3(axis, pd->dx[0], pd->dx[1], pd->dx[2])),
+                 bound_inverse(pick3(t1, pd->dx[0], pd->dx[1], pd->dx[2])),
+                 bound_inverse(pick3(t2, pd->dx[0], pd->dx[1], pd->dx[2]))},
                 global, wave};
-}
-
-// An upper bound of a cell's signal speed, velocities in pencil order.  Each
-// float rounding is below 1e-7; E - ke, which may cancel, is raised by 1e-6 of
-// its terms, the whole by 1e-5, and each speed by 1e-30 for what lies near or
-// below the smallest floats.  The pressure's floor enters as at least 1e-38;
-// a density below 1e-30 gives infinity (no bound), an overflow too.
-__device__ __forceinline__ float signal_bound(const Params &P, const float (&inv)[3], float r,
-                                              float u, float v1, float v2, float E, float e) {
-  const float g = float(P.gamma);
-  const float ke = 0.5f * __builtin_fmaf(u, u, __builtin_fmaf(v1, v1, v2 * v2));
-  const float eps = nmax(__builtin_fmaf(1e-6f, fabsf(E) + ke, E - ke), e);
-  const float floor = nmax(g * float(P.p_floor), 1e-38f);
-  const float c2 = nmax(g * (g - 1.0f) * eps, floor * __builtin_amdgcn_rcpf(r));
-  const float c = __builtin_amdgcn_sqrtf(c2) + 1e-30f;
-  const float s = __builtin_fmaf(c + fabsf(u), inv[0],
-                                 __builtin_fmaf(c + fabsf(v1), inv[1], (c + fabsf(v2)) * inv[2]));
-  return r > 1e-30f ? s * 1.00001f : __builtin_inff();
 }
 
 template <class S>
