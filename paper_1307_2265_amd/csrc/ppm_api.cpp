@@ -379,6 +379,15 @@ ppm_status ppm_fp64_ops(const double *a_dev, const double *b_dev, double *quot_d
   return e == hipSuccess ? PPM_OK : hip_fail(e, "ppm_fp64_ops");
 }
 
+ppm_status ppm_fp64_recips(const double *a_dev, const double *b_dev, double *out_dev, int64_t n,
+                           void *hip_stream) {
+  if (n < 0 || n > (int64_t(1) << 36)) return fail(PPM_EINVAL, "n must be in [0, 2^36]");
+  if (n > 0 && (!a_dev || !b_dev || !out_dev)) return fail(PPM_EINVAL, "NULL array");
+  const hipError_t e =
+      ppm::launch_fp64_recips(a_dev, b_dev, out_dev, n, static_cast<hipStream_t>(hip_stream));
+  return e == hipSuccess ? PPM_OK : hip_fail(e, "ppm_fp64_recips");
+}
+
 int64_t ppm_flux_reg_size(int32_t nx, int32_t ny, int32_t nz) {
   return 12 * (int64_t(ny) * nz + int64_t(nx) * nz + int64_t(nx) * ny);
 }

@@ -1355,6 +1355,29 @@ hipError_t launch_fp64_ops(const double *a, const double *b, double *quot, doubl
   return hipGetLastError();
 }
 
+__global__ void __launch_bounds__(256)
+fp64_recips_kernel(const double *a, const double *b, double *out, int64_t n) {
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  double inv, hc, hx;
+  out[i] = xsqrt(a[i], inv);
+  out[n + i] = inv;
+  out[2 * n + i] = xrcp(a[i]);
+  const double c = dsqrt(a[i], hc);
+  hc *= 4.0 * kInvBias;
+  const double w = c * dsqrt(b[i], hx);
+  out[3 * n + i] = w;
+  out[4 * n + i] = drcp_from(w, hx * hc);
+}
+
+hipError_t launch_fp64_recips(const double *a, const double *b, double *out, int64_t n,
+                              hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  const int64_t blocks = (n + 255) / 256;
+  hipLaunchKernelGGL(fp64_recips_kernel, dim3(unsigned(blocks)), dim3(256), 0, s, a, b, out, n);
+  return hipGetLastError();
+}
+
 // Up to kWordBlock 32-bit words by value.
 constexpr int kWordBlock = 240;
 struct WordBlock {

@@ -192,6 +192,13 @@ hipError_t launch_copy_from_siblings(const PatchDev *patches, const SiblingBox *
 hipError_t launch_fp64_ops(const double *a, const double *b, double *quot, double *root,
                            int64_t n, hipStream_t s);
 
+// The reciprocals that start from roots, and their roots, over n elements, into
+// five arrays of n one after the other: sqrt(a), its reciprocal and 1 / a as the
+// tracing takes them; W = sqrt(a) sqrt(b) and 1 / W as the two-shock solver's
+// wave speeds.
+hipError_t launch_fp64_recips(const double *a, const double *b, double *out, int64_t n,
+                              hipStream_t s);
+
 // dst[i] = words[i] for i < n (32-bit words from host memory, carried to the
 // device as kernel arguments, so no staging copy and no memset is involved).
 hipError_t launch_write_words(uint32_t *dst, const uint32_t *words, int64_t n, hipStream_t s);

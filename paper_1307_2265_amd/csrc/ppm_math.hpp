@@ -102,10 +102,10 @@ template <class T> __device__ __forceinline__ T opaque(T x) {
 // steps take four for.  (One quadratic step, 2^-48, is too little here: of 8e9
 // random operands none came out wrong, but 1 / (1 - k ulp) lies k^2 2^-106 above
 // the middle between two doubles, and a quadratic step errs downwards.)  The
-// root takes one quadratic step of the root and of its halved inverse, both
-// from below, and the correction: roots of 1 + k ulp lie as close below such a
-// middle, the side it errs to, and no operand within 2^20 ulps of any of twenty
-// centres, nor of the random ones, gave another result than sqrt.
+// root takes one quadratic step of the root and of its halved inverse h, then
+// two corrections.  h is low by up to 1.5 e^2 < 2^-47, so only roots within
+// 2^-100 of a middle can come out wrong: no operand with x = (m + 1/2)^2 + c,
+// |c| < 2000 (50 would do), does.  (With one correction 16 of these did.)
 // They omit the operand scaling and
 // special-value fix-ups that a general IEEE division or square root needs for
 // operands within 2^768 of the overflow or underflow threshold, zeros,
@@ -154,6 +154,7 @@ __device__ __forceinline__ double dsqrt(double x, double &h) {
   const double e = fma(-h, s, 0.5);
   s = fma(s, e, s);
   h = fma(h, e, h);
+  s = fma(fma(-s, s, x), h, s);
   return fma(fma(-s, s, x), h, s);
 }
 __device__ __forceinline__ double dsqrt(double x) {
@@ -478,8 +479,8 @@ template <class T> __device__ __forceinline__ FluxT<T> narrow_flux(const Flux &D
 // the shock speeds, their reciprocals and the two sides' u* at p*.
 // The loop takes about a third of a sweep (6.6 iterations on the slowest lane of a
 // wave).  One test of the count ends it, and the reciprocal speeds start from
-// the roots: 66 double instructions with three hardware estimates (each four
-// times the issue of another) an iteration instead of 74 with five.
+// the roots: 70 double instructions with three hardware estimates (each four
+// times the issue of another) an iteration instead of 77 with five.
 struct StarState {
   double ps, wl, wr, iwl, iwr, usl, usr;
 };

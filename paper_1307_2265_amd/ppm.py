@@ -84,6 +84,7 @@ SIGNATURES = {
     "ppm_graph_launch": (C.c_int, [_vp, _vp]),
     "ppm_graph_destroy": (C.c_int, [_vp]),
     "ppm_fp64_ops": (C.c_int, [_vp, _vp, _vp, _vp, C.c_int64, _vp]),
+    "ppm_fp64_recips": (C.c_int, [_vp, _vp, _vp, C.c_int64, _vp]),
     "ppm_step_cfl_noalloc": (C.c_int, [C.POINTER(ppm_patch), C.c_int32, C.c_int32, C.c_int,
                                        C.POINTER(ppm_params), _vp, C.c_int32, C.c_uint32,
                                        C.POINTER(C.c_int64), _vp]),
@@ -141,6 +142,16 @@ def ppm_fp64_ops(a, b, quot, root, stream=None) -> None:
         assert t.numel() == n and t.is_contiguous()
     _check(lib().ppm_fp64_ops(a.data_ptr(), b.data_ptr(), quot.data_ptr(), root.data_ptr(), n,
                               _stream_handle(stream)), "ppm_fp64_ops")
+
+
+def ppm_fp64_recips(a, b, out, stream=None) -> None:
+    """out[0..4] = sqrt(a), 1 / sqrt(a), 1 / a, w = sqrt(a) sqrt(b), 1 / w by the
+    library's FP64 reciprocals from roots (device float64, out of 5 n)."""
+    n = a.numel()
+    assert b.numel() == n and out.numel() == 5 * n
+    assert a.is_contiguous() and b.is_contiguous() and out.is_contiguous()
+    _check(lib().ppm_fp64_recips(a.data_ptr(), b.data_ptr(), out.data_ptr(), n,
+                                 _stream_handle(stream)), "ppm_fp64_recips")
 
 
 PPM_NOALLOC_MAX_PATCHES = 16
