@@ -1364,7 +1364,7 @@ fp64_recips_kernel(const double *a, const double *b, double *out, int64_t n) {
   out[n + i] = inv;
   out[2 * n + i] = xrcp(a[i]);
   const double c = dsqrt(a[i], hc);
-  hc *= 4.0 * kInvBias;
+  hc *= 4.0 * kInvUp;
   const double w = c * dsqrt(b[i], hx);
   out[3 * n + i] = w;
   out[4 * n + i] = drcp_from(w, hx * hc);

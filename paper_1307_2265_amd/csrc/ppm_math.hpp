@@ -92,20 +92,26 @@ template <class T> __device__ __forceinline__ T opaque(T x) {
   return x;
 }
 
-// Correctly rounded double quotient and square root for operands of
-// ordinary magnitude.  Both refine the hardware reciprocal (square root) by
-// fused multiply-adds and finish with one exact-remainder correction, which
-// yields the IEEE round-to-nearest result (Markstein's theorem; the square
-// root likewise).  The reciprocal is refined by one cubic step, y (1 + e +
-// e^2) with e = 1 - b y: the hardware estimate carries about 24 correct bits,
-// so e^3 lies near 2^-70 and three fused operations do what two quadratic
-// steps take four for.  (One quadratic step, 2^-48, is too little here: of 8e9
-// random operands none came out wrong, but 1 / (1 - k ulp) lies k^2 2^-106 above
-// the middle between two doubles, and a quadratic step errs downwards.)  The
-// root takes one quadratic step of the root and of its halved inverse h, then
-// two corrections.  h is low by up to 1.5 e^2 < 2^-47, so only roots within
-// 2^-100 of a middle can come out wrong: no operand with x = (m + 1/2)^2 + c,
-// |c| < 2000 (50 would do), does.  (With one correction 16 of these did.)
+// Correctly rounded double quotient, reciprocal and square root for operands of
+// ordinary magnitude: the hardware estimate (measured within 2^-24.1 on 16 M
+// random operands) refined by fused multiply-adds, then one exact-remainder
+// correction, which yields the IEEE round-to-nearest result (Markstein's
+// theorem) from a start that is one of the two doubles next to the exact value:
+// such a start is off by half an ulp where the exact value lies near the middle
+// between them, so the correction's own error, that half ulp times the relative
+// error of the reciprocal (of the halved inverse root) it multiplies by, is what
+// has to stay below the distance from the middle.
+//   * Reciprocal: one cubic step, y (1 + e + e^2) with e = 1 - b y, leaves e^3 <
+//     2^-73 for three fused operations (two quadratic steps take four), and the
+//     correction is right for every b but those of an all-ones mantissa, whose
+//     reciprocal (1 + 2^-53 + 2^-106) has to come out of the cubic step on the
+//     right side, and does.
+//   * Quotient: the cubic step's reciprocal is enough but where it lies on the
+//     wrong side of a middle closer than 2^-73.
+//   * Root: one quadratic step of the root and of its halved inverse h, then two
+//     corrections.  h is low by up to 1.5 e^2 < 2^-47, so only roots within
+//     2^-100 of a middle can come out wrong: no operand with x = (m + 1/2)^2 + c,
+//     |c| < 2000 (50 would do), does.  (With one correction 16 of these did.)
 // They omit the operand scaling and
 // special-value fix-ups that a general IEEE division or square root needs for
 // operands within 2^768 of the overflow or underflow threshold, zeros,
@@ -123,30 +129,32 @@ __device__ __forceinline__ double rcp_cubic(double b) {
   const double e = fma(-b, y, 1.0);
   return fma(y, fma(e, e, e), y);
 }
-// a / b from y, the correctly rounded (or, off in rare last bits, the cubic
-// step's) reciprocal of b.
+// One correction of a reciprocal y of b.
+__device__ __forceinline__ double rcp_correct(double b, double y) {
+  return fma(fma(-b, y, 1.0), y, y);
+}
+__device__ __forceinline__ double drcp(double b) { return rcp_correct(b, rcp_cubic(b)); }
+// a / b from y, the correctly rounded (or the cubic step's) reciprocal of b.
 __device__ __forceinline__ double ddiv_by(double a, double b, double y) {
   const double q = a * y;
   const double r = fma(-b, q, a);
   return fma(r, y, q);
 }
 __device__ __forceinline__ double ddiv(double a, double b) { return ddiv_by(a, b, rcp_cubic(b)); }
-__device__ __forceinline__ double drcp(double b) {
-  const double y = rcp_cubic(b);
-  return fma(fma(-b, y, 1.0), y, y);
-}
-// 1 / b from y, the reciprocal times 1 + 2^-44 to a few 2^-47 (the halved
-// inverse roots that make up b, times kInvBias): two quadratic steps, the second
-// by y again, whose excess lifts the reciprocals that end just above a middle
-// (see above) off the tie.  No hardware reciprocal: its issue takes four times
-// that of another double operation.
-constexpr double kInvBias = 1.0 + 0x1p-44;
+// 1 / b from y, the product of the halved inverse roots (each low by up to 2^-45)
+// that make up b, times 1 + 2^-43: correctly rounded for every b.  y lies above
+// the reciprocal by 2^-43 - 2^-44 at least, and the step adds 2^-41 of its move
+// too little, which leaves it above by 2^-86 to 2^-84.  So the correction's start
+// is rounded from just above: the right double, or the one above a middle that the
+// reciprocal lies just below, and from there the correction is right, the all-ones
+// mantissa included.  (Corrected by y instead of by the start, 189 of 1129
+// reciprocals next to a middle came out wrong.)  No hardware reciprocal: its issue
+// takes four times that of another double operation.
+constexpr double kInvUp = 1.0 + 0x1p-43, kInvLess = 1.0 - 0x1p-41;
 __device__ __forceinline__ double drcp_from(double b, double y) {
-  const double z = fma(fma(-b, y, 1.0), y, y);
-  return fma(fma(-b, z, 1.0), y, z);
+  return rcp_correct(b, fma(fma(-b, y, 1.0), kInvLess * y, y));
 }
-// The root, and h = 1 / (2 sqrt(x)) to about 2^-47 (never above it by more than
-// its rounding).
+// The root, and h = 1 / (2 sqrt(x)), low by up to 2^-47 (its rounding aside).
 __device__ __forceinline__ double dsqrt(double x, double &h) {
   const double y = __builtin_amdgcn_rsq(x);
   double s = x * y;
@@ -188,7 +196,7 @@ __device__ __forceinline__ double xsqrt(double x, double &inv) {
   double h;
   const double s = dsqrt(x, h);
   const double root = x == 0.0 ? x : s;
-  inv = __builtin_amdgcn_div_fixup(drcp_from(root, (2.0 * kInvBias) * h), root, 1.0);
+  inv = __builtin_amdgcn_div_fixup(drcp_from(root, (2.0 * kInvUp) * h), root, 1.0);
   return root;
 }
 
@@ -479,7 +487,7 @@ template <class T> __device__ __forceinline__ FluxT<T> narrow_flux(const Flux &D
 // the shock speeds, their reciprocals and the two sides' u* at p*.
 // The loop takes about a third of a sweep (6.6 iterations on the slowest lane of a
 // wave).  One test of the count ends it, and the reciprocal speeds start from
-// the roots: 70 double instructions with three hardware estimates (each four
+// the roots: 72 double instructions with three hardware estimates (each four
 // times the issue of another) an iteration instead of 77 with five.
 struct StarState {
   double ps, wl, wr, iwl, iwr, usl, usr;
@@ -492,8 +500,8 @@ __device__ __forceinline__ StarState two_shock_star(const Params &P, double rl, 
   double hl, hr;
   double cl = dsqrt(g * pl * rl, hl);
   double cr = dsqrt(g * pr * rr, hr);
-  hl *= 4.0 * kInvBias;  // 2 / C_s: times the halved inverse root of W_s / C_s, 1 / W_s
-  hr *= 4.0 * kInvBias;
+  hl *= 4.0 * kInvUp;  // 2 / C_s: times the halved inverse root of W_s / C_s, 1 / W_s
+  hr *= 4.0 * kInvUp;
   double ipl = drcp(pl), ipr = drcp(pr);
   double ps = nmax(ddiv(cr * pl + cl * pr - cl * cr * (ur - ul), cl + cr), P.p_floor);
   double wl, wr, iwl, iwr, usl, usr;
@@ -530,7 +538,7 @@ __device__ __forceinline__ Flux two_shock_flux(const Params &P, double rl, doubl
   double rK = left ? rl : rr, uK = left ? ul : ur, pK = left ? pl : pr;
   double iwK = left ? iwl : iwr;
   const double irK = drcp(rK);
-  double irs = irK - (ps - pK) * iwK * iwK;  // 1 / rho*, to its rounding, below too
+  double irs = irK - (ps - pK) * iwK * iwK;  // 1 / rho*, before rho* is rounded
   double rs = drcp(irs);
   if (rs < P.rho_floor) {
     rs = P.rho_floor;
@@ -551,7 +559,7 @@ __device__ __forceinline__ Flux two_shock_flux(const Params &P, double rl, doubl
     else { rb = rs; ub = us; pb = ps; }
   } else {        // rarefaction: linear through the fan
     const double head = uK + sgn * dsqrt(ddiv_by(g * pK, rK, irK));
-    const double tail = us + sgn * dsqrt(ddiv_by(g * ps, rs, irs));
+    const double tail = us + sgn * dsqrt(ddiv_by(g * ps, rs, rcp_correct(rs, irs)));
     bool outside = left ? head >= 0.0 : head <= 0.0;
     bool star = left ? tail <= 0.0 : tail >= 0.0;
     if (outside) { rb = rK; ub = uK; pb = pK; }
