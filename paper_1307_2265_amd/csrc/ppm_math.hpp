@@ -106,8 +106,10 @@ template <class T> __device__ __forceinline__ T opaque(T x) {
 //     correction is right for every b but those of an all-ones mantissa, whose
 //     reciprocal (1 + 2^-53 + 2^-106) has to come out of the cubic step on the
 //     right side, and does.
-//   * Quotient: the cubic step's reciprocal is enough but where it lies on the
-//     wrong side of a middle closer than 2^-73.
+//   * Quotient: right from the correctly rounded reciprocal of its divisor.  (From
+//     the cubic step's, which lies on the wrong side of some of the middles that
+//     are closer than 2^-73, 113 of the 207 thousand quotients by divisors less
+//     than 2^32 ulps below a power of two that this can reach were wrong.)
 //   * Root: one quadratic step of the root and of its halved inverse h, then two
 //     corrections.  h is low by up to 1.5 e^2 < 2^-47, so only roots within
 //     2^-100 of a middle can come out wrong: no operand with x = (m + 1/2)^2 + c,
@@ -134,13 +136,13 @@ __device__ __forceinline__ double rcp_correct(double b, double y) {
   return fma(fma(-b, y, 1.0), y, y);
 }
 __device__ __forceinline__ double drcp(double b) { return rcp_correct(b, rcp_cubic(b)); }
-// a / b from y, the correctly rounded (or the cubic step's) reciprocal of b.
+// a / b from y, the correctly rounded reciprocal of b.
 __device__ __forceinline__ double ddiv_by(double a, double b, double y) {
   const double q = a * y;
   const double r = fma(-b, q, a);
   return fma(r, y, q);
 }
-__device__ __forceinline__ double ddiv(double a, double b) { return ddiv_by(a, b, rcp_cubic(b)); }
+__device__ __forceinline__ double ddiv(double a, double b) { return ddiv_by(a, b, drcp(b)); }
 // 1 / b from y, the product of the halved inverse roots (each low by up to 2^-45)
 // that make up b, times 1 + 2^-43: correctly rounded for every b.  y lies above
 // the reciprocal by 2^-43 - 2^-44 at least, and the step adds 2^-41 of its move
@@ -487,7 +489,7 @@ template <class T> __device__ __forceinline__ FluxT<T> narrow_flux(const Flux &D
 // the shock speeds, their reciprocals and the two sides' u* at p*.
 // The loop takes about a third of a sweep (6.6 iterations on the slowest lane of a
 // wave).  One test of the count ends it, and the reciprocal speeds start from
-// the roots: 72 double instructions with three hardware estimates (each four
+// the roots: 74 double instructions with three hardware estimates (each four
 // times the issue of another) an iteration instead of 77 with five.
 struct StarState {
   double ps, wl, wr, iwl, iwr, usl, usr;

@@ -1,9 +1,10 @@
-"""Double reciprocals and square roots whose exact values lie nearest to the
+"""Double reciprocals, quotients and roots whose exact values lie nearest to the
 middle between two doubles, against IEEE arithmetic, bit for bit (GPU): a
 refinement that is short of a few bits, or errs to one side, shows there and
 nowhere else.  Reciprocals on both sides of a middle from the factors of 2^106 + j
 (b m = 2^106 + j with m odd, |j| < 1000, one of b = 2^53 - k among them), roots
-on both sides from m^2 + m + c = 0 modulo 2^52 or 2^53."""
+on both sides from m^2 + m + c = 0 modulo 2^52 or 2^53, quotients by divisors just
+below a power of two."""
 import numpy as np
 import pytest
 
@@ -29,6 +30,19 @@ RECIPROCALS = np.array([
     0x10318c5d4c3036, 0x15fbe3f9c7e621, 0x1f252a51329e9d, 0x12192f0aab2004, 0x15279312de8f82,
     0x16fe6c76318951, 0x143c4c6afeda3b,
 ], dtype=np.uint64).astype(np.float64) * 2.0 ** -52
+
+# a and k: a / (2^53 - k) lies as near a middle as any quotient, 1 / (2^53 - k)
+# within 2^-73 of one
+QUOTIENTS = [
+    (7724407935011299, 553393847), (7378020231649012, 600239903), (5496123684746194, 615062873),
+    (7798113501157545, 615062875), (4971568049184148, 629536921), (8106995195691211, 643685585),
+    (8622961980485001, 657529869), (8778620841357299, 671088613), (6924089366212834, 684378787),
+    (6228519934250839, 697415743), (5148843966888631, 710213429), (7995315034086201, 722784553),
+    (7241516965289050, 722784555), (5935641364162861, 735140739), (4651301520380665, 735140741),
+    (8510468517810118, 747292649), (7563203641900492, 759250091), (7044686115017426, 794042751),
+    (7683655481748075, 805306329), (6214243195827892, 805306331), (6464141998206034, 816414527),
+    (5198710519611577, 827373601), (4862944922901041, 838189401), (5500617519576225, 848867403),
+]
 
 
 @pytest.fixture(scope="module")
@@ -95,6 +109,22 @@ def test_roots_nearest_middles(P, scale):
     assert np.array_equal(o[1], 1.0 / np.sqrt(x))
     assert np.array_equal(o[3], np.sqrt(x) * np.sqrt(x[::-1]))
     assert np.array_equal(o[4], 1.0 / o[3])
+
+
+def test_quotients_nearest_middles_below_a_power_of_two(P):
+    a, b = [], []
+    for k in range(1, 2 ** 13, 2):
+        d = 2 ** 53 - k
+        for p in (53, 54):  # a 2^p = +-1 modulo d
+            i = pow(2, -p, d)
+            for v in (i, d - i):
+                if 2 ** 52 <= v < 2 ** 53:
+                    a.append(float(v))
+                    b.append(float(d))
+    assert len(a) > 4000
+    a = np.array(a + [float(v) for v, _ in QUOTIENTS])
+    b = np.array(b + [float(2 ** 53 - k) for _, k in QUOTIENTS])
+    assert np.array_equal(_ops(P, a, b)[0], a / b)
 
 
 def test_empty_and_invalid_calls(P):
