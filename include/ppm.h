@@ -424,10 +424,10 @@ ppm_status ppm_fp64_ops(const double *a_dev, const double *b_dev, double *quot_d
 /* The reciprocals that the FP64 sweeps take from roots, for the same check:
  * out_dev, 5 n doubles, gets (n of each, in this order) r = sqrt(a), 1 / r and
  * 1 / a as the characteristic tracing forms them (a in [1e-250, 1e250], zero,
- * negative or NaN, with IEEE's results), then w = sqrt(a) sqrt(b) and 1 / w as
- * the wave speeds of the two-shock solver (a, b > 0 and their product in that
- * range).  Each is the IEEE round-to-nearest result for
- * its operand as rounded.  PPM_EINVAL for n < 0 or NULL arrays. */
+ * negative, infinite or NaN, with IEEE's results), then w = sqrt(a) sqrt(b) and
+ * 1 / w as the wave speeds of the two-shock solver (a, b > 0 and their product
+ * in that range).  Each is the IEEE round-to-nearest result for its operand as
+ * rounded.  PPM_EINVAL for n < 0 or NULL arrays. */
 ppm_status ppm_fp64_recips(const double *a_dev, const double *b_dev, double *out_dev, int64_t n,
                            void *hip_stream);
 

@@ -182,8 +182,8 @@ template <> __device__ __forceinline__ float rdiv<float>(float a, float b) {
 }
 // IEEE reciprocal and square root for the characteristic tracing, whose
 // operands may also be zero, negative, infinite or NaN: the sequences above
-// with the special operands put right, by v_div_fixup and by a select for a
-// zero root (a negative or NaN operand gives NaN by itself).  They leave out
+// with the special operands put right, by v_div_fixup and by a select for the
+// root of zero and of infinity (a negative or NaN operand gives NaN by itself).  They leave out
 // only the scaling for extreme exponents: the reciprocal needs none for any
 // normal operand, and the root's operand (a product of two edge values, each
 // zero or at least an ulp of the 1e-100 floors) lies far above the 2^-900
@@ -194,10 +194,11 @@ __device__ __forceinline__ double xrcp(double b) {
 }
 __device__ __forceinline__ float xrcp(float b) { return __builtin_amdgcn_rcpf(b); }
 // The root and its reciprocal, which starts from the h of the root.
+constexpr int kZeroOrInf = 0x260;  // v_cmp_class: either zero, +infinity
 __device__ __forceinline__ double xsqrt(double x, double &inv) {
   double h;
   const double s = dsqrt(x, h);
-  const double root = x == 0.0 ? x : s;
+  const double root = __builtin_amdgcn_class(x, kZeroOrInf) ? x : s;
   inv = __builtin_amdgcn_div_fixup(drcp_from(root, (2.0 * kInvUp) * h), root, 1.0);
   return root;
 }

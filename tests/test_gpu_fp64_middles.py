@@ -127,6 +127,17 @@ def test_quotients_nearest_middles_below_a_power_of_two(P):
     assert np.array_equal(_ops(P, a, b)[0], a / b)
 
 
+def test_special_operands_of_the_tracing(P):
+    x = np.array([0.0, -0.0, 1.0, 4.0, np.inf, -1.0, -np.inf, np.nan, 1e-232, 1e232, 0.25])
+    o = _recips(P, x, np.ones_like(x))
+    with np.errstate(divide="ignore", invalid="ignore"):
+        root = np.sqrt(x)
+        want = [root, 1.0 / root, 1.0 / x]
+    for got, w in zip(o, want):
+        assert np.array_equal(got, w, equal_nan=True), (got, w)
+        assert np.array_equal(np.signbit(got[~np.isnan(w)]), np.signbit(w[~np.isnan(w)]))
+
+
 def test_empty_and_invalid_calls(P):
     import torch
     z = torch.empty(0, dtype=torch.float64, device="cuda")
