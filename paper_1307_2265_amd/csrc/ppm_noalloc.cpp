@@ -87,9 +87,11 @@ inline int tmask_of(int axis, int mask) {
   return ((mask >> t1) & 1) | (((mask >> t2) & 1) << 1);
 }
 
-// Launch shapes of the call's three sweeps, in its order: as a plan over the
-// same patches with the default tile configuration, per-sweep launches (no
-// grouped maps: each block belongs to one patch).
+// Launch shapes of the call's three sweeps, in its order: the axes swept
+// lane-parallel and the runs of a plan over the same patches with the default
+// tile configuration; the other axes marched without what needs memory of its
+// own (no grouped maps, each block belongs to one patch, and no marching by
+// halves).
 struct Shape {
   int32_t axis, mask;
   bool lanes;
@@ -190,8 +192,10 @@ extern "C" ppm_status ppm_step_cfl_noalloc(const ppm_patch *patches, int32_t npa
 
   // launch maps (prefix arrays of work chunks of the three sweeps, then the
   // CFL map) and shapes; one patch marched: whole rounds of one marching block
-  // per compute unit, the few pencils left over to the lane-parallel tail launch
-  // (as a one-patch plan does)
+  // per compute unit and the pencils left over, if at most an eighth of a round,
+  // to the lane-parallel tail launch.  (A plan's choice, which also weighs two
+  // threads to a pencil, with tails alone: 272^3 FP64 3.92 -> 3.40 ms, 400^3 10.3 ->
+  // 10.0, but mixed 300^3 3.31 -> 3.81, 320^3 3.65 -> 4.2.)
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
