@@ -160,8 +160,9 @@ int64_t ppm_flux_reg_size(int32_t nx, int32_t ny, int32_t nz);
  *                  number of pencils and compute units); the other sweeps
  *                  give each pencil to one thread that marches it.  Default 1
  *                  (x only) and, unless tile_config sets one of lanes, block,
- *                  tail and tail_round, the y and z axes too where the patches
- *                  have too few pencils to fill the device one thread each:
+ *                  tail and tail_round, or persistent=1 for several patches, the
+ *                  y and z axes too where the patches have too few pencils to
+ *                  fill the device one thread each:
  *                  ghosted transverse pencils below 208 (y) and 110 (z; in the
  *                  mixed precision 224 and 208) x the number of compute units
  *                  for one patch, 416 for several.
