@@ -569,6 +569,7 @@ ppm_status ppm_plan_create(ppm_plan **out, const ppm_patch *patches, int32_t npa
     for (int c = 0; c < 2; ++c) {
       for (int slot = 0; slot < 12; ++slot) {
         const int axis = slot / 4, tm = slot % 4;
+        if ((pl->lanes_mask >> axis) & 1) continue;
         const PatchDev &d = pl->host[0];
         const int64_t np = ppm_detail::sweep_pencils(d, axis, tm);
         const bool may_split = pl->split && cus > 0 && d.n[axis] >= 16;
