@@ -8,7 +8,8 @@
 //   * sweep_split_kernel: the marching sweep of one patch with two threads
 //     per pencil, where that leaves the device less idle.
 //   * sweep_lanes_kernel: the same sweep with the cells of a pencil across
-//     the lanes of a wave (ppm_lanes.hpp), for x sweeps.
+//     the lanes of a wave (ppm_lanes.hpp): every x sweep, and the y and z sweeps
+//     of patches with too few pencils to give each a thread.
 //   * sweep_tail_kernel: the same lane-parallel code over the last pencils of
 //     a big patch's marching sweep, one pencil per wave, after the marching
 //     launch has taken whole rounds of one block per compute unit.
@@ -139,8 +140,8 @@ sweep_kernel(const PatchDev *__restrict__ patches, const int32_t *__restrict__ c
       pc.acc = ref.acc;
     }
     const double dt = dt_dev[pd.level];
-    march_pencil<Prec, kCFL, kUseHLLC, kGrav, kGrouped ? 1 : 2>(P, pc, dt, expansion_a(P, pd.level),
-                                              march_slots(lds), 64, nfb, nfl, cfl);
+    march_pencil<Prec, kCFL, kUseHLLC, kGrav, kGrouped ? 1 : 2>(
+        P, pc, dt, expansion_a(P, pd.level), march_slots(lds), 64, nfb, nfl, cfl);
   }
   if (nfb) atomicAdd(&counters[0], (unsigned long long)nfb);
   if (nfl) atomicAdd(&counters[1], (unsigned long long)nfl);
@@ -187,7 +188,7 @@ sweep_split_kernel(const PatchDev *__restrict__ patches, int32_t axis, int32_t m
     const MarchSpan span = half ? MarchSpan{m - lead, pc.n - g + 4, m, a1, m, mine}
                                 : MarchSpan{0, m + 4, g, m - 1, 0, nullptr};
     march_pencil<Prec, kCFL, kUseHLLC, kGrav, 2>(P, pc, dt, expansion_a(P, pd.level),
-                                              march_slots(lds),64, nfb, nfl, cfl, &span);
+                                                 march_slots(lds), 64, nfb, nfl, cfl, &span);
     if (half) {
       for (int c = 0; c < kDeferCells; ++c) {
         const int64_t o = pc.base + int64_t(m + c) * pc.stride;
@@ -350,12 +351,10 @@ batch_persistent_kernel(const PatchDev *__restrict__ patches, const int32_t *__r
           const PencilRef<S> pc = make_pencil<S>(pd, axis, i1, i2);
           if (kCFL && k == 2)
             march_pencil<Prec, true, kUseHLLC, kGrav, 1>(P, pc, dt, expansion_a(P, pd.level),
-                                                      march_slots(lds), 64, nfb, nfl,
-                                                      cfl);
+                                                         march_slots(lds), 64, nfb, nfl, cfl);
           else
             march_pencil<Prec, false, kUseHLLC, kGrav, 1>(P, pc, dt, expansion_a(P, pd.level),
-                                                       march_slots(lds), 64, nfb, nfl,
-                                                       cfl);
+                                                          march_slots(lds), 64, nfb, nfl, cfl);
         }
       }
       if (kCFL && k == 2) cfl_publish(cfl, pd.level);

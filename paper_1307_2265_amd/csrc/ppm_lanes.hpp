@@ -1,7 +1,7 @@
 // ppm_lanes.hpp -- the 1-D PPM sweep with the cells of a pencil across the
 // lanes of a wave (device).
 //
-// A wavefront streams a run of consecutive pencils (rows) of one patch,
+// A wavefront streams a run of pencils (rows) of one patch, every few-th of them,
 // concatenated, through segments of 64 consecutive cells, so every load and
 // store of a sweep along x is one coalesced access per field, and every stage
 // of the update is evaluated for 64 cells at once, reading its neighbours'
@@ -177,7 +177,8 @@ __device__ __forceinline__ FluxT<typename Prec::T> sweep_segment(
   // left state of face j+1/2 (from this cell) and right state of face
   // (j-1)+1/2 (from this cell); face j+1/2 takes its right state from lane j+1
   State<T> sl, srown;
-  trace_edges<T>(gam, l, rr, dq, q6, q[1], sound_speed(gam, q[4], q[0]), tlam, rho_floor, p_floor, srown, sl);
+  trace_edges<T>(gam, l, rr, dq, q6, q[1], sound_speed(gam, q[4], q[0]), tlam, rho_floor, p_floor,
+                 srown, sl);
   const State<T> sr = state_from_right(srown);
 
   // ---- Riemann problem at face j+1/2 (faces a0-1..a1), with the optional

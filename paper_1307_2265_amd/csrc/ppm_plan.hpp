@@ -83,13 +83,15 @@ ppm::Params device_params(ppm_precision prec, const ppm_params *p);
 // (bit 0: the first transverse axis restricted to its active range, bit 1:
 // the second).
 int64_t sweep_pencils(const PatchDev &d, int axis, int tm);
-// Segments per wave run of a lane-parallel sweep over the patches, and the
-// axes that a plan sweeps that way by default (a bitmask).
+// Whether two threads march each pencil of a marching sweep, and whether the
+// pencils past its last whole round go to the lane-parallel kernel.
 struct MarchShape {
   bool split, tail;
 };
 MarchShape choose_march(int64_t np, int n, int axis, ppm_precision prec, int64_t round,
                         bool may_split, bool may_tail);
+// Segments per wave run of a lane-parallel sweep over the patches, and the
+// axes that a plan sweeps that way by default (a bitmask).
 int32_t choose_run_segments(const PatchDev *d, int32_t npatch, ppm_precision prec, int axis,
                             int tm, int cus);
 int32_t default_lanes(const PatchDev *d, int32_t npatch, ppm_precision prec, int cus);

@@ -326,7 +326,9 @@ __device__ __forceinline__ void cfl_publish(const CflAcc &a, int level) {
 // cells differently from the whole march, but no cell it writes depends on
 // them: a cell's update reaches five cells either side (the flattening of its
 // neighbours' parabolas three, the HLL fallback of a neighbouring face two
-// more), and `own_lo` is at least begin + 5 (and begin + g).  Cells own_lo ..
+// more), and `own_lo` is at least begin + 5, and begin + g + 1: the cell before it
+// has to be one this march updates (not one of its g ghosts), since the face
+// between them takes the fallback's flux where that cell goes bad.  Cells own_lo ..
 // own_hi are written (the faces between them, and below own_lo when own_lo is
 // the pencil's first active cell, are counted); cells defer_lo .. defer_lo +
 // kDeferCells - 1 go to `defer` (6 doubles per cell) instead, for the caller
@@ -352,7 +354,8 @@ struct MarchSpan {
 template <class Prec, bool kCFL, bool kUseHLLC, bool kGrav, int kUnroll>
 __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> &pc, double dt,
                              double a, double *lds_slots, int slot_stride, uint32_t &n_fallback,
-                             uint32_t &n_floor, const CflAcc &cfl, const MarchSpan *span = nullptr) {
+                             uint32_t &n_floor, const CflAcc &cfl,
+                             const MarchSpan *span = nullptr) {
   using S = typename Prec::S;
   using T = typename Prec::T;
   // with T = double the window already holds the exact pressure
@@ -528,7 +531,8 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
       }
 #pragma unroll
       for (int j = 0; j < 5; ++j) monotonize<T>(q[1][j], l[j], rr[j], dq[j], q6[j]);
-      trace_edges<T>(gam, l, rr, dq, q6, q[1][1], sound_speed(gam, q[1][4], q[1][0]), tlam, rho_floor, p_floor, rstate, lnew);
+      trace_edges<T>(gam, l, rr, dq, q6, q[1][1], sound_speed(gam, q[1][4], q[1][0]), tlam,
+                     rho_floor, p_floor, rstate, lnew);
     }
 
     // ---- 6. Riemann problem at face fc = (r-1)+1/2
