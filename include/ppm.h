@@ -182,7 +182,7 @@ int64_t ppm_flux_reg_size(int32_t nx, int32_t ny, int32_t nz);
  *                  needs every patch to hold at most 2^21 active cells
  *                  (PPM_EINVAL otherwise).  Default 0 (the per-sweep launches
  *                  were faster for every number of patches measured: 12
- *                  patches 0.06 against 1.6 ms a step, 4096 7.2 against 7.9).
+ *                  patches 0.08 against 1.5 ms a step, 4096 7.2 against 8.0).
  *   batch_block=B  threads per workgroup of the persistent launch (64..256).
  *   batch_blocks=W workgroups of the persistent launch (default: 512/B per CU).
  *   tail=0|1       one ungrouped patch: when a marching sweep's threads

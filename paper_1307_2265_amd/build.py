@@ -8,13 +8,13 @@ writes each expression in.  Packed FP32 instructions are disabled
 ppm_kernels.hip is compiled four times (PPM_KERNEL_PASS 1 to 4), so that
 each group of sweep kernels takes the LLVM machine scheduler that runs it
 fastest on gfx950 (measured, alternating runs on one box): the default one for
-the double-precision marching sweeps (256^3 last sweep 950 us; max-ilp 975,
-iterative-ilp 1130), max-ilp for the mixed-precision marching sweeps (512^3
-4.74 ms, default 4.79), every non-sweep kernel (parent interpolation from
-0.69 M cells 166 us, default 207) and the double-precision lane-parallel sweeps, and
-iterative-ilp for the mixed-precision lane-parallel ones (batch of 4096
-patches, first x sweep 2.10 ms; max-ilp 2.16, default 2.20).  Scheduling
-reorders instructions only, so results are unchanged bit for bit.
+the double-precision marching sweeps (256^3 last sweep 946 us; max-ilp 965;
+iterative-ilp stops the compiler on them), max-ilp for the mixed-precision
+marching sweeps (512^3 4.74 ms, default 4.79), every non-sweep kernel (parent
+interpolation from 0.69 M cells 166 us, default 207) and the double-precision
+lane-parallel sweeps, and iterative-ilp for the mixed-precision lane-parallel
+ones (batch of 4096 patches, first x sweep 2.10 ms; max-ilp 2.16, default 2.20).
+Scheduling reorders instructions only, so results are unchanged bit for bit.
 """
 from __future__ import annotations
 

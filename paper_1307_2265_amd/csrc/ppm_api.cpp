@@ -137,8 +137,8 @@ int64_t sweep_pencils(const PatchDev &d, int axis, int tm) {
 // in the tail costs 1.6 times its share of a marched round along y, 2.5
 // along z, whose lines lie furthest apart, 1.2 and 1.5 in the mixed precision.
 // Fitted to cubes of 264 to 450 cells, where the choice is the best or within 3 %
-// of it: FP64 y sweeps of 264 cells 1365 -> 1041 us, 320 2130 -> 1810, 380 3700 -> 2880,
-// 450 5680 -> 4800, against splitting whatever has fewer pencils than two rounds
+// of it: FP64 y sweeps of 264 cells 1445 -> 1066 us, 320 2222 -> 1869, 380 3841 -> 2968,
+// 450 5788 -> 4982, against splitting whatever has fewer pencils than two rounds
 // and a tail of at most an eighth of one.
 MarchShape choose_march(int64_t np, int n, int axis, ppm_precision prec, int64_t round,
                         bool may_split, bool may_tail) {
@@ -169,12 +169,12 @@ MarchShape choose_march(int64_t np, int n, int axis, ppm_precision prec, int64_t
 // where the latency of one wave's segments takes over, and half a wave more
 // than the mean for the uneven last round).  Over the FP64 cubes 16^3 .. 256^3
 // and the run lengths 1 .. 32 segments measured, the choice is within 9 % of
-// the best everywhere and the best or within 2 % of it on most (runs of 32
-// segments throughout took 16^3 484 us, 64^3 430 us and 128^3 1250 us a step;
-// these take 31, 121 and 480).  A y or z sweep over more data than half the
-// 256 MB of the last-level cache takes one pencil per wave: its waves share
-// lines of neighbouring pencils, which longer runs read again too late (192^3
-// y sweep 526 us with one, 655 with two).
+// the best everywhere and the best or within 2 % of it on most (y sweeps in
+// runs of 32 segments take 119 us at 16^3, 143 at 64^3 and 216 at 128^3, in these
+// 9, 41 and 162).  A y or z sweep over more data than half the 256 MB of the
+// last-level cache takes one pencil per wave: its waves share lines of
+// neighbouring pencils, which longer runs read again too late (192^3 y sweep
+// 476 us with one, 581 with two; mixed 208^3 468 and 533).
 int32_t choose_run_segments(const PatchDev *d, int32_t npatch, ppm_precision prec, int axis,
                             int tm, int cus) {
   // of thousands of patches a sample of them stands for all
@@ -210,14 +210,15 @@ int32_t choose_run_segments(const PatchDev *d, int32_t npatch, ppm_precision pre
 // A marching sweep gives each pencil to one thread (two in a plan of one
 // patch), so with few pencils its time is that of one march whatever their
 // number, while a lane-parallel sweep's falls with them.  Measured, FP64
-// (mixed), us a sweep: 128^3 y 142 lane-parallel, 279 marching (111 and
-// 235); 208^3 y 592 and 640 (440 and 538), z 755 and 700 (457 and 548); 224^3 y
-// 762 and 799, z 1480 and 760 (703 and 708); 232^3 y 872 and 792 (617 and 730), z
-// (652 and 588); 240^3 y 958 and 824 (678 and 612); 160^3 z 262 and 359, 164^3 z
-// 396 and 372, 192^3 z 717 and 578.  A z
+// (mixed), us a sweep: 128^3 y 150 lane-parallel, 292 marching (114 and
+// 228); 208^3 y 608 and 667 (446 and 530), z 767 and 741 (447 and 532); 224^3 y
+// 807 and 827 (552 and 650), z 1502 and 794 (699 and 696); 232^3 y 869 and 824
+// (631 and 710), z (645 and 566); 240^3 y 969 and 861 (695 and 601); 160^3 z 280
+// and 368, 164^3 z 381 and 382, 192^3 z 723 and 598.  A z
 // sweep's lanes lie a plane apart, hence its earlier end.  Several patches of
-// 8^3 .. 32^3, us a step: 12 patches 62 and 328, 100 (60 thousand pencils a
-// sweep) 262 and 413 (193 and 317), 300 (180 thousand) 798 and 712.
+// 8^3 .. 32^3, us a step: 12 patches 78 and 324 (69 and 249), 100 (60 thousand
+// pencils a sweep) 266 and 393 (195 and 298), 300 (180 thousand) 710 and 631 (492
+// and 423).
 int32_t default_lanes(const PatchDev *d, int32_t npatch, ppm_precision prec, int cus) {
   int64_t np[2] = {0, 0};
   for (int32_t i = 0; i < npatch; ++i)

@@ -257,10 +257,12 @@ __device__ __forceinline__ void stream_pencils(const PatchDev *__restrict__ patc
 
 // Lane-parallel sweep: each wavefront streams rows_per_wave(n, segs) pencils.
 // Four waves per SIMD; the builds that take the next timestep or carry the
-// gravity terms would spill there, and a reload that waits for the stores of
-// the segment before it costs more than the fourth wave gives (three waves:
-// mixed 512^3 last x sweep 5.62 -> 5.10 ms, FP64 8.43 -> 8.13, 128^3 with gravity
-// 181 -> 171 us; mixed without either 4.88 -> 4.98, hence four).
+// gravity terms spill there, and a reload that waits for the stores of the
+// segment before it mostly costs more than the fourth wave gives (four against
+// three waves: mixed 512^3 last x sweep 4.81 and 4.71 ms, HLLC with diffusion on
+// 97 x 61 x 83 cells 50 and 46 us, 128^3 with gravity the same within 3 %; FP64
+// two-shock is the exception, 512^3 7.76 and 7.87 ms, 128^3 126 and 133 us; mixed
+// without either 4.88 and 4.98, hence four).
 template <class Prec, bool kCFL, bool kUseHLLC, bool kGrav>
 __global__ void __launch_bounds__(kMaxBlock, kCFL || kGrav ? 3 : 4)
 sweep_lanes_kernel(const PatchDev *__restrict__ patches, const int32_t *__restrict__ chunk_start,

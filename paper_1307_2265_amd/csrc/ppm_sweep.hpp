@@ -344,8 +344,8 @@ struct MarchSpan {
 // take the signal speed of every cell written (the sweep must then be the
 // last of its step).
 // The marching loop holds kUnroll iterations: two spare half the moves that
-// carry the window on (512^3 y sweep mixed 4.74 -> 4.52 ms, FP64 6.78 -> 6.60,
-// 256^3 last sweep by halves 950 -> 925 us); over several patches, where
+// carry the window on (512^3 y sweep mixed 4.74 -> 4.52 ms, FP64 7.37 -> 7.26,
+// 256^3 last sweep by halves 988 -> 942 us); over several patches, where
 // pencils are short, one is as fast or faster (4096-patch batch, mixed y sweep
 // 1335 us, 1370 with two).
 // a: the level's expansion factor (1 for the static equations).  kGrav: the
@@ -453,10 +453,11 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
   }
 
   // The last round of two may hold one iteration too many.  Marching by halves it
-  // is run (256^3 y sweep 972 -> 922 us, mixed 700 -> 686): it reads cells of the
+  // is run (256^3 y sweep 983 -> 965 us, mixed 700 -> 686): it reads cells of the
   // patch only, and neither counts nor writes, the cell it would finish not
-  // being an owned one.  The FP64 build that takes the timestep would spill, and
-  // leaves the loop instead (925 us against 1014), as the whole march does (the same).
+  // being an owned one.  The FP64 build that takes the timestep would spill more,
+  // and leaves the loop instead (942 us against 1008), as the whole march does (the
+  // same).
   for (int kk = begin; kk <= kend; kk += kUnroll)
 #pragma unroll
   for (int step = 0; step < kUnroll; ++step) {
