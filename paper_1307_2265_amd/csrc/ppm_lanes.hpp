@@ -123,7 +123,7 @@ __device__ __forceinline__ FluxT<typename Prec::T> sweep_segment(
     qp[k] = from_right(q[k]);
   }
   const double rEm = from_left(rE), rEp = from_right(rE);
-  const double m3 = nmax(nmax(rEm, rE), rEp);
+  const double m3 = vmax<double>(vmax<double>(rEm, rE), rEp);
 
   // ---- limited slopes (cells 1..n-2), density second difference
   T dm[5];
@@ -162,7 +162,7 @@ __device__ __forceinline__ FluxT<typename Prec::T> sweep_segment(
   if (flatten) {
     const T ftm = from_left(ft), ftp = from_right(ft);
     T fn = (qp[4] - qm[4] > T(0)) ? ftm : ftp;
-    T f = nmax(ft, fn);
+    T f = vmax<T>(ft, fn);
     if (f != T(0)) {
 #pragma unroll
       for (int k = 0; k < 5; ++k) {

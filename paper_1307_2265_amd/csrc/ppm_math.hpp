@@ -65,13 +65,18 @@ __device__ __forceinline__ double expansion_a(const Params &P, int level) {
 template <class T> __device__ __forceinline__ T vmin(T a, T b) { return a < b ? a : b; }
 template <class T> __device__ __forceinline__ T vmax(T a, T b) { return a > b ? a : b; }
 // Minimum and maximum as one instruction each (the ternary forms above cost a
-// compare and two selects per double); a NaN operand gives the other one.
+// compare and two selects per double); a NaN operand gives the other one.  They
+// serve only where that changes no result: a NaN velocity, density or pressure of
+// a cell already makes the velocity of its traced states, and so every flux that
+// samples one, NaN.  Where a NaN cell is seen without entering a flux (the
+// pressure floor, the flattening, the neighbourhood's largest rho E) the
+// comparisons stay as the method has them.
 __device__ __forceinline__ double nmin(double a, double b) { return __builtin_fmin(a, b); }
 __device__ __forceinline__ float nmin(float a, float b) { return __builtin_fminf(a, b); }
 __device__ __forceinline__ double nmax(double a, double b) { return __builtin_fmax(a, b); }
 __device__ __forceinline__ float nmax(float a, float b) { return __builtin_fmaxf(a, b); }
 template <class T> __device__ __forceinline__ T clamp01(T x) {
-  return nmin(nmax(x, T(0)), T(1));
+  return x < T(0) ? T(0) : (x > T(1) ? T(1) : x);
 }
 __device__ __forceinline__ double csign(double a, double b) { return __builtin_copysign(a, b); }
 __device__ __forceinline__ float csign(float a, float b) { return __builtin_copysignf(a, b); }
@@ -226,7 +231,8 @@ __device__ __forceinline__ double eos_pressure(const Params &P, double rho, doub
                                                double v2, double E, double e) {
   double eps = xfma(-0.5, u * u + v1 * v1 + v2 * v2, E);
   if ((P.flags & kDualEnergy) && !ratio_above(eps, E, P.eta1)) eps = e;
-  return nmax(P.gm1 * rho * eps, P.p_floor);
+  const double p = P.gm1 * rho * eps;
+  return p < P.p_floor ? P.p_floor : p;
 }
 __device__ __forceinline__ void eos(const Params &P, double rho, double u, double v1, double v2,
                                     double E, double e, double &p, double &c) {
@@ -436,10 +442,12 @@ __device__ __forceinline__ void trace_edges(double g, const T (&l)[5], const T (
   const T sr = pos ? slow : zero, sl = neg ? slow : zero;
   const T kr = up > T(0) ? -zero * er.iC : zero;  // the reference waves' own
   const T kl = um < T(0) ? zero * el.iC : zero;
-  right = edge_state<T>(er, kr, sr, pos ? b0 : zero, pos ? v1 : r[2], pos ? v2 : r[3], rho_floor,
-                        p_floor);
-  left = edge_state<T>(el, sl, kl, neg ? b0 : zero, neg ? v1 : l[2], neg ? v2 : l[3], rho_floor,
-                       p_floor);
+  // an average over no domain is the edge value, or NaN where the parabola is
+  auto still = [&](const T (&edge)[5], int k) { return xfma(zero, dq[k], edge[k]); };
+  right = edge_state<T>(er, kr, sr, pos ? b0 : zero, pos ? v1 : still(r, 2),
+                        pos ? v2 : still(r, 3), rho_floor, p_floor);
+  left = edge_state<T>(el, sl, kl, neg ? b0 : zero, neg ? v1 : still(l, 2),
+                       neg ? v2 : still(l, 3), rho_floor, p_floor);
 }
 
 // Face flux in the flux type T of a precision: the mass and momentum fluxes

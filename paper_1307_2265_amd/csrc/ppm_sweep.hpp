@@ -483,7 +483,7 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
       q[4][0] = T(r); q[4][1] = T(u); q[4][2] = T(v1); q[4][3] = T(v2); q[4][4] = T(p);
       if (!kExactP) pd[4] = p;
       rE[2] = r * E;
-      m3[4] = nmax(nmax(rE[0], rE[1]), rE[2]);  // of cell k-1
+      m3[4] = vmax<double>(vmax<double>(rE[0], rE[1]), rE[2]);  // of cell k-1
     }
     // ---- 2. slope and second difference of cell k-2, 3. interface value
     // between cells k-3 and k-2 (as late as the parabola of cell k-3 allows:
@@ -521,7 +521,7 @@ __device__ void march_pencil(const Params &P, const PencilRef<typename Prec::S> 
       }
       if (flatten) {
         T fn = (q[2][4] - q[0][4] > T(0)) ? ft[0] : ft[2];
-        T f = nmax(ft[1], fn);
+        T f = vmax<T>(ft[1], fn);
         if (f != T(0)) {
 #pragma unroll
           for (int j = 0; j < 5; ++j) {
