@@ -109,9 +109,10 @@ typedef struct {
   void *rho, *vx, *vy, *vz; /* double (PPM_FP64) or float (PPM_MIXED) */
   double *etot, *eint;      /* double in both precisions.  Every cell a sweep
                                reads, ghosts included, must hold a physical
-                               state: finite values, rho >= rho_floor, and
-                               magnitudes below 1e100 (results for other
-                               input are unspecified; none is detected) */
+                               state: finite values, rho >= rho_floor,
+                               magnitudes below 1e100 and a density times
+                               pressure below 1e200 (results for other input
+                               are unspecified; none is detected) */
   double *flux_reg;         /* nullable; ppm_flux_reg_size(nx,ny,nz) doubles */
   const void *gx, *gy, *gz; /* nullable (all three or none): gravitational
                                acceleration at the cell centres at the half

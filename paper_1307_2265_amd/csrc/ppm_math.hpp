@@ -127,8 +127,10 @@ template <class T> __device__ __forceinline__ T opaque(T x) {
 // at least 1e-100 are enforced at the interface), the Lagrangian wave speeds
 // and the two-shock star density are positive and finite for such states, and
 // the steepening and flattening ratios divide differences of floored cell
-// values; with state magnitudes below 1e100 every operand there is far inside
-// the range, and the results are bit for bit those of a / b and sqrt(x).  The
+// values; with state magnitudes below 1e100 and rho p below 1e200 (from 1e204 on
+// the cube of an inverse impedance in the two-shock solver leaves the normal
+// numbers) every operand there is inside the range, and the results are bit for
+// bit those of a / b and sqrt(x).  The
 // characteristic tracing, whose reconstructed edge values no floor bounds
 // (an edge density or pressure can be zero), uses xrcp / xsqrt instead.
 __device__ __forceinline__ double rcp_cubic(double b) {
